@@ -85,8 +85,9 @@ int mg_nn_forward(mg_nn *nn, int64_t nbox, const float *x, float *y);
  *   mean over boxes and cells of (network(x[idx[q]]) - target[idx[q]])^2
  * for q < nbox (idx: device int32, or NULL for the identity) and its
  * gradient with respect to the FP32 parameters (the BF16 rounding of the
- * weights taken as the identity; FP32 arithmetic on the vector units) into
- * the network's gradient buffer.  ws (device, 256-byte aligned) must hold
+ * weights taken as the identity; FP32 gradients, each split exactly into
+ * three BF16 parts for the matrix cores, FP32 accumulation) into the
+ * network's gradient buffer.  ws (device, 256-byte aligned) must hold
  * mg_nn_train_bytes(nbox) bytes.  loss (host) may be NULL; when given the
  * call synchronises the stream.  mg_nn_get_grad copies the gradient to the
  * host.  mg_nn_adam applies one Adam update (Kingma & Ba) to the

@@ -19,7 +19,8 @@
 //  * layer 3 first forms Q[tap][cell] = sum_c W3[c][tap] a2[c][cell] with
 //    16x16x16 MFMAs (N = taps), then y[cell] = b3 + sum_tap Q[tap][cell+tap-1],
 //    which turns the 16->1 convolution into a dense GEMM plus a 27-term sum.
-// The backward pass (training only) runs in FP32 on the vector units.
+// The backward pass (training only) keeps its FP32 gradients: each is split
+// exactly into three BF16 parts for the matrix cores.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -35,6 +36,8 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kW1 = 0, kB1 = 432, kW2 = 448, kB2 = 7360, kW3 = 7376, kB3 = 7808;
 constexpr int kP1 = 0, kP2 = 512, kP3 = 512 + 18 * 512;  // offsets in the packed fragments
@@ -48,8 +51,6 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
 // The same rounding (nearest even) by the hardware conversion; a NaN stays a
 // NaN (its payload may differ from f2bf's).  Two values per instruction.
 __device__ __forceinline__ uint16_t f2bf_hw(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
-__device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-__device__ __forceinline__ float round_bf(float f) { return bf2f(f2bf(f)); }
 // max(z, 0) that propagates NaN (a non-finite weight must reach the output)
 __device__ __forceinline__ float relu(float z) { return !(z <= 0.0f) ? z : 0.0f; }
 
@@ -79,28 +80,29 @@ __device__ __forceinline__ T block_sum256(T v, T *S) {
 // ------------------------------------------------------------ weight packing
 // Fragments in the lane order of the MFMA B operand (lane l holds column
 // l % 16, K rows 8 (l / 16) .. +7 for 16x16x32, 4 (l / 16) .. +3 for 16x16x16).
+// One entry a thread: 2 us (one workgroup walking all entries: 12 us).
 __global__ __launch_bounds__(256) void k_nn_pack(const float *__restrict__ prm, uint16_t *__restrict__ pk) {
-    for (int e = threadIdx.x; e < kNnPacked; e += 256) {
-        float v = 0.0f;
-        if (e < kP2) {
-            int lane = e >> 3, q = e & 7, o = lane & 15, g = lane >> 4, t = 8 * g + q;
-            if (t < 27) v = prm[kW1 + o * 27 + t];
-        } else if (e < kP3) {
-            // fragment f = (2 dk + type) 3 + di: type 0 has kernel rows dj = 0
-            // in K groups 0-1 and dj = 1 in groups 2-3, type 1 dj = 2 in
-            // groups 0-1 and zeros in 2-3
-            int e2 = e - kP2, f = e2 >> 9, r = e2 & 511, lane = r >> 3, q = r & 7;
-            int dk = f / 6, type = (f / 3) & 1, di = f % 3, o = lane & 15, g = lane >> 4, ch = 8 * (g & 1) + q;
-            int dj = type == 0 ? (g < 2 ? 0 : 1) : (g < 2 ? 2 : -1);
-            if (dj >= 0) v = prm[kW2 + (o * 16 + ch) * 27 + (dk * 3 + dj) * 3 + di];
-        } else {
-            int e3 = e - kP3, nt = e3 >> 8, r = e3 & 255, lane = r >> 2, q = r & 3;
-            int n = lane & 15, g = lane >> 4, tap = 16 * nt + n, ch = 4 * g + q;
-            if (tap < 27) v = prm[kW3 + ch * 27 + tap];
-        }
-        pk[e] = f2bf(v);
+    const int e = blockIdx.x * 256 + threadIdx.x;  // grid: kNnPacked / 256
+    float v = 0.0f;
+    if (e < kP2) {
+        int lane = e >> 3, q = e & 7, o = lane & 15, g = lane >> 4, t = 8 * g + q;
+        if (t < 27) v = prm[kW1 + o * 27 + t];
+    } else if (e < kP3) {
+        // fragment f = (2 dk + type) 3 + di: type 0 has kernel rows dj = 0
+        // in K groups 0-1 and dj = 1 in groups 2-3, type 1 dj = 2 in
+        // groups 0-1 and zeros in 2-3
+        int e2 = e - kP2, f = e2 >> 9, r = e2 & 511, lane = r >> 3, q = r & 7;
+        int dk = f / 6, type = (f / 3) & 1, di = f % 3, o = lane & 15, g = lane >> 4, ch = 8 * (g & 1) + q;
+        int dj = type == 0 ? (g < 2 ? 0 : 1) : (g < 2 ? 2 : -1);
+        if (dj >= 0) v = prm[kW2 + (o * 16 + ch) * 27 + (dk * 3 + dj) * 3 + di];
+    } else {
+        int e3 = e - kP3, nt = e3 >> 8, r = e3 & 255, lane = r >> 2, q = r & 3;
+        int n = lane & 15, g = lane >> 4, tap = 16 * nt + n, ch = 4 * g + q;
+        if (tap < 27) v = prm[kW3 + ch * 27 + tap];
     }
+    pk[e] = f2bf(v);
 }
+static_assert(kNnPacked % 256 == 0, "one thread per packed entry");
 
 // ------------------------------------------------------------------ forward
 // x [nbox][1000] FP32 (10^3, x fastest), y [nbox][512] FP32 (natural order).
@@ -220,19 +222,17 @@ __global__ __launch_bounds__(kFwdThreads) __attribute__((amdgpu_waves_per_eu(3, 
             }
             bf16x8 A = __builtin_bit_cast(bf16x8, make_uint4(wv[0], wv[1], wv[2], wv[3]));
             f32x4 D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, B1, zero, 0, 0, 0);
+            u16x4 av;
 #pragma unroll
             for (int r = 0; r < 4; r++) {
                 int c = 16 * m + 4 * g + r, pi = c & 7, pj = (c >> 3) & 7, pk3 = c >> 6;
-                A1[(pk3 + 1) * kA1z + (pj + 1) * kA1y + (pi + 1) * 16 + o] = f2bf_hw(relu(D[r] + bias1));
+                av[r] = f2bf_hw(relu(D[r] + bias1));
+                A1[(pk3 + 1) * kA1z + (pj + 1) * kA1y + (pi + 1) * 16 + o] = av[r];
             }
+            // a1 for training, [box][channel][cell]: the lane's four cells
+            if (SAVE) *reinterpret_cast<u16x4 *>(a1o + q * 8192 + (o * 512 + 4 * g + 16 * m)) = av;
         }
         __syncthreads();
-        if (SAVE)  // a1 for training, [box][channel][cell]
-            for (int e = t; e < 8192; e += kFwdThreads) {
-                int ch = e >> 9, c = e & 511;
-                a1o[(q * 16 + ch) * 512 + c] =
-                    A1[((c >> 6) + 1) * kA1z + (((c >> 3) & 7) + 1) * kA1y + ((c & 7) + 1) * 16 + ch];
-            }
         // ---- layer 2, blocked along z: wave w owns the output tiles of
         // y-rows (2w, 2w+1) at every z.  Each padded input slice zs is loaded
         // once (per x-shift di: the kernel rows dj = 0 | 1 in K groups 0-1 |
@@ -268,21 +268,19 @@ __global__ __launch_bounds__(kFwdThreads) __attribute__((amdgpu_waves_per_eu(3, 
                 const int kd = zs - 2;  // the output slice completed by this input slice
                 if (kd >= 0) {
                     const int m = 4 * kd + w;
+                    u16x4 av;
 #pragma unroll
                     for (int r = 0; r < 4; r++) {
                         int c = 16 * m + 4 * g + r;
-                        A2[c * 16 + o] = f2bf_hw(relu(acc[kd % 3][r] + bias2));
+                        av[r] = f2bf_hw(relu(acc[kd % 3][r] + bias2));
+                        A2[c * 16 + o] = av[r];
                     }
+                    if (SAVE) *reinterpret_cast<u16x4 *>(a2o + q * 8192 + (o * 512 + 4 * g + 16 * m)) = av;
                     acc[kd % 3] = zero;
                 }
             }
         }
         __syncthreads();  // A1 is dead; its space holds Q from here on
-        if (SAVE)  // a2 for training, [box][channel][cell]
-            for (int e = t; e < 8192; e += kFwdThreads) {
-                int ch = e >> 9, c = e & 511;
-                a2o[(q * 16 + ch) * 512 + c] = A2[c * 16 + ch];
-            }
         // ---- layer 3: Q[tap][cell] = sum_c W3[c][tap] a2[c][cell], taps
         // 0-15 now and 16-26 after the first half of the sum
 #pragma unroll 2
@@ -326,213 +324,385 @@ __global__ __launch_bounds__(kFwdThreads) __attribute__((amdgpu_waves_per_eu(3, 
 }
 
 // ----------------------------------------------------------------- backward
-// Loss = mean over boxes and cells of (y - target)^2; gy = 2 (y - target) / N.
-// Per box: gz2 = (transposed conv of gy with W3) * [a2 > 0] and
-// gz1 = (transposed conv of gz2 with W2) * [a1 > 0], with the BF16-rounded
-// weights the forward used.  Also the box's sum of squared errors.
-__global__ __launch_bounds__(256) void k_nn_bwd_act(const float *__restrict__ y,
-                                                    const float *__restrict__ tgt,
-                                                    const int32_t *__restrict__ idx,
-                                                    const uint16_t *__restrict__ a1o,
-                                                    const uint16_t *__restrict__ a2o,
-                                                    const float *__restrict__ prm, float scale2,
-                                                    float *__restrict__ gz2o, float *__restrict__ gz1o,
-                                                    double *__restrict__ lossp) {
-    __shared__ float gyp[1000];
-    __shared__ float W3s[432];
-    __shared__ __attribute__((aligned(16))) float W2s[27 * 16 * 16];  // [tap][o][i]
-    __shared__ float G2[16 * 1000];
-    __shared__ double S[4];
-    const int64_t q = blockIdx.x;
-    const int64_t src = idx ? (int64_t)idx[q] : q;
-    const int t = threadIdx.x;
-    for (int e = t; e < 1000; e += 256) gyp[e] = 0.0f;
-    for (int e = t; e < 16000; e += 256) G2[e] = 0.0f;
-    for (int e = t; e < 432; e += 256) W3s[e] = round_bf(prm[kW3 + e]);
-    for (int e = t; e < 6912; e += 256) {
-        int tp = e % 27, oi = e / 27, o = oi >> 4, i = oi & 15;  // prm index (o*16 + i)*27 + tp
-        W2s[(tp * 16 + o) * 16 + i] = round_bf(prm[kW2 + e]);
+// Loss = mean over boxes and cells of (y - target)^2; gy = 2 (y - target) / N,
+// gz2 = (transposed conv of gy with W3) * [a2 > 0], gz1 = (transposed conv of
+// gz2 with W2) * [a1 > 0], and the weight gradients dW3 = <gy, a2>, dW2 =
+// <gz2, a1>, dW1 = <gz1, x> over the cells, with the BF16-rounded weights the
+// forward used.  Every product has one BF16 factor (a weight, an activation
+// or the input) and one FP32 factor g.  The FP32 one is split exactly into
+// three BF16 values g = hi + mid + lo (8 significand bits each, by
+// truncation), so three BF16 MFMAs give the exact products with FP32
+// accumulation: no gradient is rounded below 32 bits.
+struct Split3 {
+    uint32_t p[3];  // BF16 patterns in the high halves
+};
+__device__ __forceinline__ Split3 split3(float v) {
+    Split3 s;
+    s.p[0] = __float_as_uint(v) & 0xffff0000u;
+    // a non-finite value is its own high part (inf - inf would turn it into a NaN)
+    float r = v - __uint_as_float(s.p[0]);
+    r = __builtin_isfinite(v) ? r : 0.0f;
+    s.p[1] = __float_as_uint(r) & 0xffff0000u;
+    s.p[2] = __float_as_uint(r - __uint_as_float(s.p[1]));
+    return s;
+}
+// Eight values as three MFMA operands (a lane's eight K entries)
+__device__ __forceinline__ void split_frag(const float v[8], bf16x8 f[3]) {
+    u32x4 d[3];
+#pragma unroll
+    for (int h = 0; h < 4; h++) {
+        const Split3 a = split3(v[2 * h]), b = split3(v[2 * h + 1]);
+#pragma unroll
+        for (int s = 0; s < 3; s++) d[s][h] = (a.p[s] >> 16) | (b.p[s] & 0xffff0000u);
     }
-    __syncthreads();
-    double ls = 0.0;
-    for (int c = t; c < 512; c += 256) {
-        float d = y[q * 512 + c] - tgt[src * 512 + c];
-        ls += (double)d * (double)d;
-        int i = c & 7, j = (c >> 3) & 7, k = c >> 6;
-        gyp[((k + 1) * 10 + j + 1) * 10 + i + 1] = scale2 * d;
+#pragma unroll
+    for (int s = 0; s < 3; s++) f[s] = __builtin_bit_cast(bf16x8, d[s]);
+}
+__device__ __forceinline__ f32x4 mfma32(bf16x8 a, bf16x8 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+// Eight consecutive BF16 values from position e of an LDS array (a lane's
+// eight x-neighbours; e may be odd): five dwords, shifted by a half.
+__device__ __forceinline__ bf16x8 row8(const uint16_t *p, int e) {
+    const uint32_t *d = reinterpret_cast<const uint32_t *>(p) + (e >> 1);
+    const uint32_t sh = (e & 1) * 16;
+    u32x4 o;
+    uint32_t lo = d[0];
+#pragma unroll
+    for (int h = 0; h < 4; h++) {
+        const uint32_t hi = d[h + 1];
+        o[h] = __builtin_amdgcn_alignbit(hi, lo, sh);
+        lo = hi;
     }
-    double tot = block_sum256(ls, S);
-    if (t == 0) lossp[q] = tot;
-    __syncthreads();
-    for (int c = t; c < 512; c += 256) {
-        int i = c & 7, j = (c >> 3) & 7, k = c >> 6;
-        float acc[16];
-#pragma unroll
-        for (int a = 0; a < 16; a++) acc[a] = 0.0f;
-        for (int tp = 0; tp < 27; tp++) {
-            int di = tp % 3, dj = (tp / 3) % 3, dk = tp / 9;
-            float gv = gyp[((k - dk + 2) * 10 + j - dj + 2) * 10 + i - di + 2];
-#pragma unroll
-            for (int a = 0; a < 16; a++) acc[a] += W3s[a * 27 + tp] * gv;
-        }
-#pragma unroll
-        for (int a = 0; a < 16; a++) {
-            uint16_t bits = a2o[(q * 16 + a) * 512 + c];
-            float g2 = (bits & 0x7fff) ? acc[a] : 0.0f;
-            G2[a * 1000 + ((k + 1) * 10 + j + 1) * 10 + i + 1] = g2;
-            gz2o[(q * 16 + a) * 512 + c] = g2;
-        }
-    }
-    __syncthreads();
-    for (int c = t; c < 512; c += 256) {
-        int i = c & 7, j = (c >> 3) & 7, k = c >> 6;
-        float acc[16];
-#pragma unroll
-        for (int a = 0; a < 16; a++) acc[a] = 0.0f;
-        for (int tp = 0; tp < 27; tp++) {
-            int di = tp % 3, dj = (tp / 3) % 3, dk = tp / 9;
-            int sidx = ((k - dk + 2) * 10 + j - dj + 2) * 10 + i - di + 2;
-            for (int o = 0; o < 16; o++) {
-                float gv = G2[o * 1000 + sidx];
-                const float4 *wr = reinterpret_cast<const float4 *>(W2s + (tp * 16 + o) * 16);
-#pragma unroll
-                for (int v4 = 0; v4 < 4; v4++) {
-                    float4 wv = wr[v4];
-                    acc[4 * v4 + 0] += wv.x * gv;
-                    acc[4 * v4 + 1] += wv.y * gv;
-                    acc[4 * v4 + 2] += wv.z * gv;
-                    acc[4 * v4 + 3] += wv.w * gv;
-                }
-            }
-        }
-#pragma unroll
-        for (int a = 0; a < 16; a++) {
-            uint16_t bits = a1o[(q * 16 + a) * 512 + c];
-            gz1o[(q * 16 + a) * 512 + c] = (bits & 0x7fff) ? acc[a] : 0.0f;
-        }
-    }
+    return __builtin_bit_cast(bf16x8, o);
 }
 
-// Weight gradients: block r sums over boxes r, r + gridDim.x, ... and writes
-// its partial gradient (parameter order) to part[r][kNnParams].
-__global__ __launch_bounds__(256) void k_nn_wgrad(const float *__restrict__ x,
-                                                  const float *__restrict__ y,
-                                                  const float *__restrict__ tgt,
-                                                  const int32_t *__restrict__ idx, int64_t nbox,
-                                                  float scale2, const uint16_t *__restrict__ a1o,
-                                                  const uint16_t *__restrict__ a2o,
-                                                  const float *__restrict__ gz2o,
-                                                  const float *__restrict__ gz1o,
-                                                  float *__restrict__ part) {
-    __shared__ uint16_t U[16 * 1000];  // a1 or a2, zero-padded 10^3 per channel
-    __shared__ float V[16 * 512];      // gz2 or gz1
-    __shared__ float X[1000];          // input (BF16-rounded) or gy
-    const int t = threadIdx.x;
-    const int o2 = t >> 4, c2 = t & 15;  // dW2 entry (o2, c2, all taps)
-    float acc2[27];
+// Operand fragments of the transposed convolutions, in k_nn_pack's lane
+// order: first W2 with input and output channels and the tap direction
+// exchanged (18 fragments, rows paired as in the forward), then W3 [27 taps,
+// padded to 32][16 channels].
+constexpr int kPT3 = 18 * 512, kPackedT = kPT3 + 512;
+static_assert(kPackedT % 256 == 0 && kPackedT * 2 <= kNnParams * 4, "one thread per entry; fits in one partial gradient");
+__global__ __launch_bounds__(256) void k_nn_pack_t(const float *__restrict__ prm, uint16_t *__restrict__ pk) {
+    const int e = blockIdx.x * 256 + threadIdx.x;  // grid: kPackedT / 256
+    const int lane = (e & 511) >> 3, q = e & 7, n = lane & 15, g = lane >> 4;
+    float v = 0.0f;
+    if (e < kPT3) {
+        const int f = e >> 9, dk = f / 6, type = (f / 3) & 1, di = f % 3, o = 8 * (g & 1) + q;
+        const int dj = type == 0 ? (g < 2 ? 0 : 1) : (g < 2 ? 2 : -1);
+        if (dj >= 0) v = prm[kW2 + (o * 16 + n) * 27 + ((2 - dk) * 3 + 2 - dj) * 3 + 2 - di];
+    } else if (8 * g + q < 27) {
+        v = prm[kW3 + n * 27 + 8 * g + q];
+    }
+    pk[e] = f2bf(v);
+}
+
+// gy of box q into three zero-padded 10^3 arrays of BF16 parts (positions
+// kGyLen apart); the padding is cleared once, before the first box.
+constexpr int kGyLen = 1016;
+__device__ __forceinline__ void gy_store(uint16_t *gys, int c, float v) {
+    const Split3 s = split3(v);
+    const int at = (((c >> 6) + 1) * 10 + ((c >> 3) & 7) + 1) * 10 + (c & 7) + 1;
 #pragma unroll
-    for (int tp = 0; tp < 27; tp++) acc2[tp] = 0.0f;
-    float db2 = 0.0f, acc1[2] = {0.0f, 0.0f}, acc3[2] = {0.0f, 0.0f};
+    for (int h = 0; h < 3; h++) gys[h * kGyLen + at] = (uint16_t)(s.p[h] >> 16);
+}
+
+// gz2, gz1 (FP32, [box][channel][cell]) and the box's sum of squared errors.
+// Persistent workgroups of 4 waves, one box at a time; tiles of 16 cells as in
+// the forward, wave w owning the tiles of y-rows (2w, 2w+1), so that gz2 stays
+// in the registers of the wave that formed it.  gz2 is one MFMA per part and
+// tile (K = 27 taps); gz1 is the forward's z-blocked layer 2 on the transposed
+// weights, once per part of gz2, which goes through one padded LDS buffer
+// [cell][channel] in turn while the eight output tiles accumulate in
+// registers.  Bound by the LDS reads of the padded buffer (180 16-byte reads
+// a lane and box) and the 432 MFMAs a wave and box: 40 us for 1024 boxes
+// (FP32 multiply-adds, each reading one LDS operand, took 299 us).
+constexpr int kNnActBlocks = 512;  // 2 per CU: at 3 (168 registers) the weights, gz2 and the eight sums spill
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_nn_bwd_act(
+    const float *__restrict__ y, const float *__restrict__ tgt, const int32_t *__restrict__ idx, int64_t nbox,
+    const uint16_t *__restrict__ a1o, const uint16_t *__restrict__ a2o, const uint16_t *__restrict__ pkt,
+    float scale2, float *__restrict__ gz2o, float *__restrict__ gz1o, double *__restrict__ lossp) {
+    constexpr int kGy = 168, kGz = 10 * kGy, kG = 10 * kGz;  // as A1 in the forward
+    __shared__ __attribute__((aligned(16))) uint16_t G[kG];
+    __shared__ __attribute__((aligned(16))) uint16_t gys[3 * kGyLen];
+    __shared__ double S[4];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6, row = lane & 15, g = lane >> 4, n = lane & 15;
+    const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    bf16x8 B2[18];
+#pragma unroll
+    for (int f = 0; f < 18; f++)
+        B2[f] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(pkt + (f * 64 + lane) * 8));
+    const bf16x8 B3 = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(pkt + kPT3 + lane * 8));
+    // this lane's eight taps of gy, from its cell of the wave's tile at k = 0
+    // (taps 27-31 are masked to 0: their weights are, but 0 * inf is not)
+    const uint16_t *gt[8];
+    uint32_t tm[4];
+#pragma unroll
+    for (int h = 0; h < 8; h++) {
+        const int tp = 8 * g + h < 27 ? 8 * g + h : 26;
+        gt[h] = gys + 222 + (2 * w + (row >> 3)) * 10 + (row & 7) - tap_off(tp);
+        if (!(h & 1)) tm[h >> 1] = (8 * g + h < 27 ? 0xffffu : 0u) | (8 * g + h + 1 < 27 ? 0xffff0000u : 0u);
+    }
+    // the padding of both buffers stays 0: only interior cells are written
+    for (int e = t; e < kG / 8; e += 256) reinterpret_cast<uint4 *>(G)[e] = make_uint4(0, 0, 0, 0);
+    for (int e = t; e < 3 * kGyLen / 8; e += 256) reinterpret_cast<uint4 *>(gys)[e] = make_uint4(0, 0, 0, 0);
     for (int64_t q = blockIdx.x; q < nbox; q += gridDim.x) {
         const int64_t src = idx ? (int64_t)idx[q] : q;
-        // ---- dW2, db2
-        for (int e = t; e < 16000; e += 256) {
-            int ch = e / 1000, p = e - ch * 1000, pi = p % 10, pj = (p / 10) % 10, pk = p / 100;
-            uint16_t v = 0;
-            if (pi >= 1 && pi <= 8 && pj >= 1 && pj <= 8 && pk >= 1 && pk <= 8)
-                v = a1o[(q * 16 + ch) * 512 + ((pk - 1) * 8 + pj - 1) * 8 + pi - 1];
-            U[e] = v;
-        }
-        for (int e = t; e < 8192; e += 256) V[e] = gz2o[q * 8192 + e];
-        __syncthreads();
-        for (int c = 0; c < 512; c++) {
-            int i = c & 7, j = (c >> 3) & 7, k = c >> 6;
-            float gv = V[o2 * 512 + c];
-            int base = c2 * 1000 + (k * 10 + j) * 10 + i;
+        __syncthreads();  // the buffers are cleared, or the previous box is done with them
+        double ls = 0.0;
 #pragma unroll
-            for (int tp = 0; tp < 27; tp++) acc2[tp] += gv * bf2f(U[base + tap_off(tp)]);
-            db2 += gv;
+        for (int h = 0; h < 2; h++) {
+            const int c = t + 256 * h;
+            const float d = y[q * 512 + c] - tgt[src * 512 + c];
+            ls += (double)d * (double)d;
+            gy_store(gys, c, scale2 * d);
         }
-        __syncthreads();
-        // ---- dW1, db1
-        for (int e = t; e < 1000; e += 256) X[e] = round_bf(x[src * 1000 + e]);
-        for (int e = t; e < 8192; e += 256) V[e] = gz1o[q * 8192 + e];
-        __syncthreads();
+        const double tot = block_sum256(ls, S);  // also orders the writes of gys before the reads below
+        if (t == 0) lossp[q] = tot;
+        f32x4 gz2[8];
 #pragma unroll
-        for (int s = 0; s < 2; s++) {
-            int p = t + 256 * s;
-            if (p < 432) {
-                int o = p / 27, tp = p % 27, off = tap_off(tp);
-                float a = 0.0f;
-                for (int c = 0; c < 512; c++) {
-                    int i = c & 7, j = (c >> 3) & 7, k = c >> 6;
-                    a += V[o * 512 + c] * X[(k * 10 + j) * 10 + i + off];
+        for (int k = 0; k < 8; k++) {
+            const int m = 4 * k + w;
+            const u16x4 mask = *reinterpret_cast<const u16x4 *>(a2o + (q * 16 + n) * 512 + 16 * m + 4 * g);
+            f32x4 D = zero;
+#pragma unroll
+            for (int s = 0; s < 3; s++) {
+                u32x4 A;
+#pragma unroll
+                for (int h = 0; h < 4; h++)
+                    A[h] = tm[h] & (gt[2 * h][s * kGyLen + k * 100] |
+                                    ((uint32_t)gt[2 * h + 1][s * kGyLen + k * 100] << 16));
+                D = mfma32(__builtin_bit_cast(bf16x8, A), B3, D);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; r++) gz2[k][r] = (mask[r] & 0x7fff) ? D[r] : 0.0f;
+            *reinterpret_cast<f32x4 *>(gz2o + (q * 16 + n) * 512 + 16 * m + 4 * g) = gz2[k];
+            __builtin_amdgcn_sched_barrier(0);  // one tile's gathers at a time: hoisted, they spill
+        }
+        f32x4 acc[8];
+#pragma unroll
+        for (int k = 0; k < 8; k++) acc[k] = zero;
+        const int i = row & 7, jj = 2 * w + (row >> 3);
+        const int colA = (g < 2 ? 0 : 1) * kGy, colB = 2 * kGy;  // kernel row of each K group
+#pragma unroll 1
+        for (int s = 0; s < 3; s++) {
+            if (s > 0) __syncthreads();  // the previous part has been read
+#pragma unroll
+            for (int k = 0; k < 8; k++) {
+#pragma unroll
+                for (int r = 0; r < 4; r++) {
+                    const int cr = 4 * g + r;  // cell within the tile: x, and which of the two y-rows
+                    const uint32_t u = __float_as_uint(gz2[k][r]);
+                    G[(k + 1) * kGz + (2 * w + (cr >> 3) + 1) * kGy + ((cr & 7) + 1) * 16 + n] = (uint16_t)(u >> 16);
+                    // what is left for the next part
+                    gz2[k][r] = __builtin_isfinite(gz2[k][r])
+                                    ? gz2[k][r] - __uint_as_float(u & 0xffff0000u) : 0.0f;
                 }
-                acc1[s] += a;
-            } else if (p < 448) {
-                float a = 0.0f;
-                for (int c = 0; c < 512; c++) a += V[(p - 432) * 512 + c];
-                acc1[s] += a;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int zs = 0; zs < 10; zs++) {
+                const uint16_t *src2 = G + zs * kGz + jj * kGy + i * 16 + 8 * (g & 1);
+                uint4 FA[3], FB[3];
+#pragma unroll
+                for (int di = 0; di < 3; di++) {
+                    FA[di] = *reinterpret_cast<const uint4 *>(src2 + colA + di * 16);
+                    FB[di] = g < 2 ? *reinterpret_cast<const uint4 *>(src2 + colB + di * 16) : make_uint4(0, 0, 0, 0);
+                }
+#pragma unroll
+                for (int dk = 0; dk < 3; dk++) {
+                    const int k = zs - dk;
+                    if (k < 0 || k > 7) continue;
+#pragma unroll
+                    for (int di = 0; di < 3; di++) {
+                        acc[k] = mfma32(__builtin_bit_cast(bf16x8, FA[di]), B2[(dk * 2 + 0) * 3 + di], acc[k]);
+                        acc[k] = mfma32(__builtin_bit_cast(bf16x8, FB[di]), B2[(dk * 2 + 1) * 3 + di], acc[k]);
+                    }
+                }
+                if (zs & 1) __builtin_amdgcn_sched_barrier(0);  // two slices' loads in flight
             }
         }
-        __syncthreads();
-        // ---- dW3, db3
-        for (int e = t; e < 16000; e += 256) {
-            int ch = e / 1000, p = e - ch * 1000, pi = p % 10, pj = (p / 10) % 10, pk = p / 100;
-            uint16_t v = 0;
-            if (pi >= 1 && pi <= 8 && pj >= 1 && pj <= 8 && pk >= 1 && pk <= 8)
-                v = a2o[(q * 16 + ch) * 512 + ((pk - 1) * 8 + pj - 1) * 8 + pi - 1];
-            U[e] = v;
-        }
-        for (int c = t; c < 512; c += 256) X[c] = scale2 * (y[q * 512 + c] - tgt[src * 512 + c]);
-        __syncthreads();
 #pragma unroll
-        for (int s = 0; s < 2; s++) {
-            int p = t + 256 * s;
-            if (p < 432) {
-                int ch = p / 27, tp = p % 27, off = tap_off(tp);
-                float a = 0.0f;
-                for (int c = 0; c < 512; c++) {
-                    int i = c & 7, j = (c >> 3) & 7, k = c >> 6;
-                    a += X[c] * bf2f(U[ch * 1000 + (k * 10 + j) * 10 + i + off]);
-                }
-                acc3[s] += a;
-            } else if (p == 432) {
-                float a = 0.0f;
-                for (int c = 0; c < 512; c++) a += X[c];
-                acc3[s] += a;
-            }
-        }
-        __syncthreads();
-    }
-    float *pr = part + (int64_t)blockIdx.x * kNnParams;
+        for (int k = 0; k < 8; k++) {
+            const int64_t at = (q * 16 + n) * 512 + 16 * (4 * k + w) + 4 * g;
+            const u16x4 mask = *reinterpret_cast<const u16x4 *>(a1o + at);
+            f32x4 o;
 #pragma unroll
-    for (int tp = 0; tp < 27; tp++) pr[kW2 + (o2 * 16 + c2) * 27 + tp] = acc2[tp];
-    if (c2 == 0) pr[kB2 + o2] = db2;
-#pragma unroll
-    for (int s = 0; s < 2; s++) {
-        int p = t + 256 * s;
-        if (p < 432) {
-            pr[kW1 + p] = acc1[s];
-            pr[kW3 + p] = acc3[s];
-        } else if (p < 448) {
-            pr[kB1 + p - 432] = acc1[s];
-            if (p == 432) pr[kB3] = acc3[s];
+            for (int r = 0; r < 4; r++) o[r] = (mask[r] & 0x7fff) ? acc[k][r] : 0.0f;
+            *reinterpret_cast<f32x4 *>(gz1o + at) = o;
         }
     }
 }
 
-// grad[p] = sum over blocks of part[block][p] (fixed order, FP64); block 0's
-// thread 0 also writes the mean squared error.
+// Weight gradients: workgroup r sums over boxes r, r + gridDim.x, ... in MFMA
+// accumulators and writes its partial gradient (parameter order) to
+// part[r][kNnParams].  Each product is a GEMM over the 512 cells, 32 (four
+// x-rows) a step, the steps dealt to the four waves: a lane's eight K entries
+// are one x-row.
+//  dW2[o][c][tap]: rows o = gz2 (read once, straight from memory, and split),
+//    columns c = a1 shifted by the tap: 27 accumulators; a1 sits zero-padded
+//    and channel-major in LDS, and one read of a row of 10 serves the three
+//    x-shifts.
+//  dW1[o][tap]: rows o = gz1, columns the taps of x (27 of 32; column 27 is
+//    ones and gives db1).
+//  dW3[c][tap]: rows c = a2 (straight from memory), columns the taps of gy.
+// 1024 boxes: 44 us, bound by the latency of the two workgroups a CU that the
+// 27 accumulators allow (an FP32 vector version with one LDS read per
+// multiply-add took 633 us).
+constexpr int kUrow = 12, kUch = 1204;  // u16 per padded x-row (8-byte rows) and per channel
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_nn_wgrad(
+    const float *__restrict__ x, const float *__restrict__ y, const float *__restrict__ tgt,
+    const int32_t *__restrict__ idx, int64_t nbox, float scale2, const uint16_t *__restrict__ a1o,
+    const uint16_t *__restrict__ a2o, const float *__restrict__ gz2o, const float *__restrict__ gz1o,
+    float *__restrict__ part) {
+    __shared__ __attribute__((aligned(16))) uint16_t U[16 * kUch];
+    __shared__ __attribute__((aligned(16))) uint16_t xs[1016];
+    __shared__ __attribute__((aligned(16))) uint16_t gys[3 * kGyLen];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6, n = lane & 15, g = lane >> 4;
+    const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    f32x4 acc2[27], acc1[2], acc3[2];
+#pragma unroll
+    for (int tp = 0; tp < 27; tp++) acc2[tp] = zero;
+    acc1[0] = acc1[1] = acc3[0] = acc3[1] = zero;
+    float db2 = 0.0f, db3 = 0.0f;
+    // tap of this lane's column in the two column tiles (columns 27-31 are unused or ones)
+    int xoff[2], goff[2];
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+        const int tp = 16 * h + n < 27 ? 16 * h + n : 0;
+        xoff[h] = tap_off(tp);
+        goff[h] = 222 - tap_off(tp);
+    }
+    const bool ones = n == 27 - 16;
+    for (int e = t; e < 16 * kUch / 4; e += 256) reinterpret_cast<uint2 *>(U)[e] = make_uint2(0, 0);
+    for (int e = t; e < 3 * kGyLen / 8; e += 256) reinterpret_cast<uint4 *>(gys)[e] = make_uint4(0, 0, 0, 0);
+    if (t < 16) xs[1000 + t] = 0;
+    for (int64_t q = blockIdx.x; q < nbox; q += gridDim.x) {
+        const int64_t src = idx ? (int64_t)idx[q] : q;
+        __syncthreads();
+#pragma unroll
+        for (int h = 0; h < 4; h++) {  // row r of 64 of channel ch, written one cell to the right
+            const int e = t + 256 * h, ch = e >> 6, r = e & 63;
+            const uint4 v = *reinterpret_cast<const uint4 *>(a1o + (q * 16 + ch) * 512 + r * 8);
+            uint32_t *d = reinterpret_cast<uint32_t *>(U + ch * kUch + (((r >> 3) + 1) * 10 + (r & 7) + 1) * kUrow);
+            *reinterpret_cast<uint2 *>(d) = make_uint2(v.x << 16, __builtin_amdgcn_alignbit(v.y, v.x, 16));
+            *reinterpret_cast<uint2 *>(d + 2) =
+                make_uint2(__builtin_amdgcn_alignbit(v.z, v.y, 16), __builtin_amdgcn_alignbit(v.w, v.z, 16));
+            d[4] = v.w >> 16;
+        }
+#pragma unroll
+        for (int h = 0; h < 4; h++)
+            if (t + 256 * h < 1000) xs[t + 256 * h] = f2bf(x[src * 1000 + t + 256 * h]);
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            const int c = t + 256 * h;
+            const float v = scale2 * (y[q * 512 + c] - tgt[src * 512 + c]);
+            db3 += v;
+            gy_store(gys, c, v);
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (int st = 0; st < 4; st++) {
+            const int k = 2 * w + (st >> 1), j = 4 * (st & 1) + g;  // this lane's x-row
+            const int64_t at = (q * 16 + n) * 512 + (k * 8 + j) * 8;
+            float v2[8], v1[8];
+            *reinterpret_cast<f32x4 *>(v2) = *reinterpret_cast<const f32x4 *>(gz2o + at);
+            *reinterpret_cast<f32x4 *>(v2 + 4) = *reinterpret_cast<const f32x4 *>(gz2o + at + 4);
+            *reinterpret_cast<f32x4 *>(v1) = *reinterpret_cast<const f32x4 *>(gz1o + at);
+            *reinterpret_cast<f32x4 *>(v1 + 4) = *reinterpret_cast<const f32x4 *>(gz1o + at + 4);
+            const bf16x8 a2 = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(a2o + at));
+            db2 += ((v2[0] + v2[1]) + (v2[2] + v2[3])) + ((v2[4] + v2[5]) + (v2[6] + v2[7]));
+            bf16x8 A[3];
+            split_frag(v2, A);
+#pragma unroll
+            for (int r = 0; r < 9; r++) {  // kernel rows (dk, dj) = (r / 3, r % 3)
+                const uint32_t *d = reinterpret_cast<const uint32_t *>(
+                    U + n * kUch + ((k + r / 3) * 10 + j + r % 3) * kUrow);
+                const uint2 d01 = *reinterpret_cast<const uint2 *>(d), d23 = *reinterpret_cast<const uint2 *>(d + 2);
+                const uint32_t d4 = d[4];
+                const u32x4 b[3] = {{d01.x, d01.y, d23.x, d23.y},
+                                    {__builtin_amdgcn_alignbit(d01.y, d01.x, 16),
+                                     __builtin_amdgcn_alignbit(d23.x, d01.y, 16),
+                                     __builtin_amdgcn_alignbit(d23.y, d23.x, 16),
+                                     __builtin_amdgcn_alignbit(d4, d23.y, 16)},
+                                    {d01.y, d23.x, d23.y, d4}};
+#pragma unroll
+                for (int s = 0; s < 3; s++)
+#pragma unroll
+                    for (int di = 0; di < 3; di++)
+                        acc2[3 * r + di] = mfma32(A[s], __builtin_bit_cast(bf16x8, b[di]), acc2[3 * r + di]);
+            }
+            split_frag(v1, A);
+            const int rowx = (k * 10 + j) * 10;
+            bf16x8 X[2] = {row8(xs, rowx + xoff[0]), row8(xs, rowx + xoff[1])};
+            const u32x4 one = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+            if (ones) X[1] = __builtin_bit_cast(bf16x8, one);
+#pragma unroll
+            for (int s = 0; s < 3; s++)
+#pragma unroll
+                for (int h = 0; h < 2; h++) {
+                    acc1[h] = mfma32(A[s], X[h], acc1[h]);
+                    acc3[h] = mfma32(a2, row8(gys + s * kGyLen, rowx + goff[h]), acc3[h]);
+                }
+        }
+    }
+    // the four waves' sums, added in wave order in LDS and written by all
+    float *P = reinterpret_cast<float *>(U);  // dW2 [16][16][27], then dW1, db1 [16][28], dW3 [16][27], db2 [16], db3
+    constexpr int oP1 = 6912, oP3 = oP1 + 448, oPb = oP3 + 432;
+    static_assert((oPb + 17) * 4 <= 16 * kUch * 2, "the sums fit in the activations' space");
+    db2 += __shfl_xor(db2, 16);
+    db2 += __shfl_xor(db2, 32);
+    for (int off = 32; off > 0; off >>= 1) db3 += __shfl_xor(db3, off);
+    for (int v = 0; v < 4; v++) {
+        __syncthreads();
+        if (v != w) continue;
+        auto add = [&](int at, float val) { P[at] = v ? P[at] + val : val; };
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const int o = 4 * g + r;
+#pragma unroll
+            for (int tp = 0; tp < 27; tp++) add((o * 16 + n) * 27 + tp, acc2[tp][r]);
+#pragma unroll
+            for (int h = 0; h < 2; h++) {
+                if (16 * h + n < 28) add(oP1 + o * 28 + 16 * h + n, acc1[h][r]);
+                if (16 * h + n < 27) add(oP3 + o * 27 + 16 * h + n, acc3[h][r]);
+            }
+        }
+        if (lane < 16) add(oPb + n, db2);
+        if (lane == 0) add(oPb + 16, db3);
+    }
+    __syncthreads();
+    float *pr = part + (int64_t)blockIdx.x * kNnParams;
+    for (int e = t; e < kNnParams; e += 256) {
+        int at;
+        if (e < kB1) at = oP1 + e / 27 * 28 + e % 27;
+        else if (e < kW2) at = oP1 + (e - kB1) * 28 + 27;
+        else if (e < kB2) at = e - kW2;
+        else if (e < kW3) at = oPb + e - kB2;
+        else if (e < kB3) at = oP3 + e - kW3;
+        else at = oPb + 16;
+        pr[e] = P[at];
+    }
+}
+
+// grad[p] = sum over workgroups of part[r][p] (FP64, fixed order: 8 strided
+// sums, then their sum); block 0 also writes the mean squared error.  32
+// parameters x 8 rows a block: the rows of a parameter are summed by 8
+// threads instead of one (512 rows: 7 us against 132, a chain of 512 loads).
 __global__ __launch_bounds__(256) void k_nn_reduce(const float *__restrict__ part, int nblk,
                                                    const double *__restrict__ lossp, int64_t nbox,
                                                    float *__restrict__ grad, double *__restrict__ loss) {
-    int p = blockIdx.x * 256 + threadIdx.x;
+    __shared__ double R[8][32];
+    const int t = threadIdx.x, c = t & 31, rw = t >> 5, p = blockIdx.x * 32 + c;
+    double s = 0.0;
     if (p < kNnParams) {
-        double s = 0.0;
-        for (int r = 0; r < nblk; r++) s += (double)part[(int64_t)r * kNnParams + p];
-        grad[p] = (float)s;
+#pragma unroll 8
+        for (int r = rw; r < nblk; r += 8) s += (double)part[(int64_t)r * kNnParams + p];
     }
+    R[rw][c] = s;
+    __syncthreads();
+    if (rw == 0 && p < kNnParams)
+        grad[p] = (float)(((R[0][c] + R[1][c]) + (R[2][c] + R[3][c])) + ((R[4][c] + R[5][c]) + (R[6][c] + R[7][c])));
     if (blockIdx.x == 0) {
         __shared__ double S[4];
         double v = 0.0;
@@ -748,7 +918,7 @@ int64_t nn_train_layout(int64_t nbox, char *base, NnTrainWs *w) {
 }
 
 void launch_nn_pack(const float *prm, uint16_t *pk, hipStream_t s) {
-    hipLaunchKernelGGL(k_nn_pack, dim3(1), dim3(256), 0, s, prm, pk);
+    hipLaunchKernelGGL(k_nn_pack, dim3(kNnPacked / 256), dim3(256), 0, s, prm, pk);
 }
 
 void launch_nn_forward(const float *prm, const uint16_t *pk, int64_t nbox, const int32_t *idx,
@@ -767,12 +937,17 @@ void launch_nn_backward(const float *prm, int64_t nbox, const int32_t *idx, cons
                         const float *target, const NnTrainWs &w, float *grad, hipStream_t s) {
     if (nbox <= 0) return;
     float scale2 = (float)(2.0 / (512.0 * (double)nbox));
-    hipLaunchKernelGGL(k_nn_bwd_act, dim3((unsigned)nbox), dim3(256), 0, s, w.y, target, idx, w.a1,
-                       w.a2, prm, scale2, w.gz2, w.gz1, w.lossp);
+    // the partial gradients' buffer holds the transposed weights until the
+    // weight-gradient kernel writes it
+    uint16_t *pkt = reinterpret_cast<uint16_t *>(w.part);
+    hipLaunchKernelGGL(k_nn_pack_t, dim3(kPackedT / 256), dim3(256), 0, s, prm, pkt);
+    unsigned grid = (unsigned)(nbox < kNnActBlocks ? nbox : kNnActBlocks);
+    hipLaunchKernelGGL(k_nn_bwd_act, dim3(grid), dim3(256), 0, s, w.y, target, idx, nbox, w.a1, w.a2,
+                       (const uint16_t *)pkt, scale2, w.gz2, w.gz1, w.lossp);
     int nblk = (int)nn_wgrad_blocks(nbox);
     hipLaunchKernelGGL(k_nn_wgrad, dim3((unsigned)nblk), dim3(256), 0, s, x, w.y, target, idx, nbox,
                        scale2, w.a1, w.a2, w.gz2, w.gz1, w.part);
-    hipLaunchKernelGGL(k_nn_reduce, dim3((kNnParams + 255) / 256), dim3(256), 0, s, w.part, nblk,
+    hipLaunchKernelGGL(k_nn_reduce, dim3((kNnParams + 31) / 32), dim3(256), 0, s, w.part, nblk,
                        w.lossp, nbox, grad, w.loss);
 }
 

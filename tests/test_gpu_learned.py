@@ -123,6 +123,47 @@ def test_gradient_parity(nbox, indexed):
         assert e <= GRAD_REL, (name, e)
 
 
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("nbox,scale", [(1, 1e12), (2, 1e-12), (513, 1.0), (1025, 1.0)])
+def test_gradient_keeps_32_bits(nbox, scale):
+    """The backward kernels split each FP32 gradient factor into three BF16
+    parts.  Bar 2e-4: an activation that FP32 and FP64 round to different BF16
+    neighbours (one in 2^13, 2^-9 relative) puts the gradients about 3e-5
+    apart, while a factor rounded to BF16 (2^-9 relative, uniform) would put
+    them 1e-3 apart.  513 and 1025 boxes: one more than the grids (512
+    workgroups) and than two rounds of them."""
+    say("gradient split nbox", nbox, "scale", scale)
+    p = rand_params(17)
+    x = rand_x(18, nbox)
+    tgt = (scale * np.random.default_rng(19).standard_normal((nbox, 8, 8, 8))).astype(np.float32)
+    net = NN.Net(p)
+    loss = net.gradient(torch.from_numpy(x).cuda(), torch.from_numpy(tgt).cuda())
+    g = net.get_grad().astype(np.float64)
+    L, ref = N.gradients(p.astype(np.float64), x.astype(np.float64), tgt.astype(np.float64))
+    assert abs(loss - L) <= 1e-4 * L
+    for name, lo, n in segments():
+        e = rel_l2(g[lo:lo + n], ref[lo:lo + n])
+        say("  ", name, "rel", e)
+        assert e <= 2e-4, (name, e)
+
+
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+def test_gradient_carries_non_finite_targets(bad):
+    """A non-finite target reaches the loss and the last bias' gradient as the
+    value itself (the split of a factor into BF16 parts must not turn an
+    infinity into a NaN), and every layer's gradient as non-finite values."""
+    say("gradient non-finite", bad)
+    net = NN.Net(rand_params(20))
+    tgt = np.zeros((2, 8, 8, 8), dtype=np.float32)
+    tgt[1, 3, 4, 5] = bad
+    loss = net.gradient(torch.from_numpy(rand_x(21, 2)).cuda(), torch.from_numpy(tgt).cuda())
+    g = net.get_grad()
+    assert np.isnan(loss) if np.isnan(bad) else loss == np.inf
+    assert np.isnan(g[-1]) if np.isnan(bad) else g[-1] == -bad
+    for name, lo, n in segments():
+        assert not np.isfinite(g[lo:lo + n]).all(), name
+
+
 def test_gradient_with_index_equals_gathered_batch():
     say("gradient index")
     p = rand_params(10)
