@@ -1953,39 +1953,53 @@ __global__ __launch_bounds__(256) void k_face_xt(const int32_t *__restrict__ nbr
 // r = (sx+1) + 3 (sy+1) + 9 (sz+1), where along each axis s = -1 takes cells
 // 0..2, s = +1 cells 5..7 and s = 0 all cells (so r = 13 is the whole box
 // and the 26 others the cells within 3 of each face, edge and corner).
+//
+// A region is a product of ranges, so the maxima are taken axis by axis: one
+// wavefront per box, lane = x-row (its 8 cells are 4 consecutive values of
+// each colour), then along y and z through LDS: 192, 72 and 27 maxima of at
+// most 8 values instead of 27 of 512.  Bound by reading b (4 KB a box); the
+// direct form, 27 running maxima a thread and 162 FP64 shuffles a wave, took
+// 139 us on 9001 boxes, this one 10.8 (3.6 TB/s).  The maximum (fmax: a NaN cell is skipped) does not
+// depend on the order.
 __global__ __launch_bounds__(256) void k_refine_scores(Geo g, const double *__restrict__ rhs, int64_t n,
                                                        double *__restrict__ scores) {
-    __shared__ double W[4][27];
-    int64_t b = xcd_map(blockIdx.x, n);
-    if (b >= n) return;
-    int t = threadIdx.x;
-    int l = g.ijk[b * 4 + 3];
-    double h = g.len / (8.0 * (double)(1 << (l - 1)));
-    double m[27];
-#pragma unroll
-    for (int r = 0; r < 27; r++) m[r] = 0.0;
-#pragma unroll
-    for (int c = 0; c < 2; c++) {
-        int q = c * 256 + t, mm = q & 3, j = (q >> 2) & 7, k = (q >> 5) & 7;
-        int i = 2 * mm + ((j + k + c) & 1);
-        double v = fabs(rhs[b * 512 + q]) * (h * h);
-        bool lo[3] = {i <= 2, j <= 2, k <= 2}, hi[3] = {i >= 5, j >= 5, k >= 5};
-#pragma unroll
-        for (int r = 0; r < 27; r++) {
-            int sx = r % 3 - 1, sy = (r / 3) % 3 - 1, sz = r / 9 - 1;
-            bool in = (sx == 0 || (sx < 0 ? lo[0] : hi[0])) && (sy == 0 || (sy < 0 ? lo[1] : hi[1])) &&
-                      (sz == 0 || (sz < 0 ? lo[2] : hi[2]));
-            if (in) m[r] = fmax(m[r], v);
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < 27; r++) {
-        double v = m[r];
-        for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off));
-        if ((t & 63) == 0) W[t >> 6][r] = v;
+    __shared__ double X[4][3 * 64], Y[4][9 * 8];
+    const int w = threadIdx.x >> 6, t = threadIdx.x & 63;
+    const int64_t nblk = (n + 3) >> 2, blk = xcd_map(blockIdx.x, nblk);
+    if (blk >= nblk) return;
+    const int64_t b = 4 * blk + w;
+    const bool on = b < n;  // wave-uniform
+    if (on) {
+        const double h = g.len / (8.0 * (double)(1 << (g.ijk[b * 4 + 3] - 1))), h2 = h * h;
+        const double4 c0 = ld_stream(reinterpret_cast<const double4 *>(rhs + b * 512) + t);
+        const double4 c1 = ld_stream(reinterpret_cast<const double4 *>(rhs + b * 512 + 256) + t);
+        const bool odd = ((t & 7) + (t >> 3)) & 1;  // the row's first cell is of colour 1
+        auto v = [h2](double x) __attribute__((always_inline)) { return fabs(x) * h2; };
+        const double e0 = v(odd ? c1.x : c0.x), o0 = v(odd ? c0.x : c1.x), e1 = v(odd ? c1.y : c0.y);
+        const double o1 = v(odd ? c0.y : c1.y), e2 = v(odd ? c1.z : c0.z), o2 = v(odd ? c0.z : c1.z);
+        const double e3 = v(odd ? c1.w : c0.w), o3 = v(odd ? c0.w : c1.w);
+        const double lo = fmax(fmax(fmax(0.0, e0), o0), e1), hi = fmax(fmax(fmax(0.0, o2), e3), o3);
+        X[w][t] = lo;
+        X[w][64 + t] = fmax(fmax(lo, hi), fmax(o1, e2));
+        X[w][128 + t] = hi;
     }
     __syncthreads();
-    if (t < 27) scores[b * 27 + t] = fmax(fmax(W[0][t], W[1][t]), fmax(W[2][t], W[3][t]));
+    if (on)
+        for (int e = t; e < 72; e += 64) {  // e = region of (x, y) * 8 + k
+            const int k = e & 7, sx = (e >> 3) % 3, sy = (e >> 3) / 3;
+            const double *r = X[w] + 64 * sx + 8 * k;
+            double m = 0.0;
+            for (int j = sy == 2 ? 5 : 0; j < (sy == 0 ? 3 : 8); j++) m = fmax(m, r[j]);
+            Y[w][e] = m;
+        }
+    __syncthreads();
+    if (on && t < 27) {
+        const int sz = t / 9;
+        const double *r = Y[w] + 8 * (t % 9);
+        double m = 0.0;
+        for (int k = sz == 2 ? 5 : 0; k < (sz == 0 ? 3 : 8); k++) m = fmax(m, r[k]);
+        scores[b * 27 + t] = m;
+    }
 }
 
 // The refinement criterion with its 3-cell buffer (section 2.5) reduced to
@@ -1993,27 +2007,35 @@ __global__ __launch_bounds__(256) void k_refine_scores(Geo g, const double *__re
 // cells and the cells of its same-level leaf neighbours within 3 cells of
 // it (region 26 - o of neighbour b + o; a missing or refined neighbour
 // contributes b's own whole-box score r = 13); 0 for a refined box.  The
-// maximum is taken as (m < x) ? x : m in the order o = 0..26, the host
-// planner's arithmetic, so the two give the same bits.
+// maximum is taken as (m < x) ? x : m in the order o = 0..26 from m = the
+// box's own score, the host planner's arithmetic, so the two give the same
+// bits: the pairwise maximum below keeps the first of equal values, and a
+// NaN x, which never replaces m, enters as m.
+//
+// 32 lanes a box, one neighbour each: three dependent loads instead of 27 x 3
+// in turn (9001 boxes: 3.9 us; one thread a box: 18 us, the latency of 36
+// blocks).
 __global__ __launch_bounds__(256) void k_refine_near(const int32_t *__restrict__ n27,
                                                      const int32_t *__restrict__ isleaf,
                                                      const double *__restrict__ sc, int64_t n,
                                                      double *__restrict__ near) {
-    int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (b >= n) return;
-    if (!isleaf[b]) {
-        near[b] = 0.0;
-        return;
+    const int64_t b = 8 * (int64_t)blockIdx.x + (threadIdx.x >> 5);
+    const int o = threadIdx.x & 31;
+    if (b >= n) return;  // whole groups of 32 lanes
+    const bool leaf = isleaf[b] != 0;
+    const double own = sc[27 * b + 13];
+    double m = own;
+    if (leaf && o < 27) {
+        const int32_t N = n27[27 * b + o];
+        if (N >= 0 && isleaf[N]) m = sc[27 * (int64_t)N + (26 - o)];
+        if (m != m) m = own;
     }
-    const int32_t *nb = n27 + 27 * b;
-    double m = sc[27 * b + 13];
-    for (int o = 0; o < 27; o++) {
-        int32_t N = nb[o];
-        bool use = N >= 0 && isleaf[N];
-        double x = sc[use ? 27 * (int64_t)N + (26 - o) : 27 * b + 13];
-        m = (m < x) ? x : m;
+    for (int off = 1; off < 32; off <<= 1) {
+        const double p = __shfl_xor(m, off);
+        const double first = (o & off) ? p : m, second = (o & off) ? m : p;
+        m = (first < second) ? second : first;
     }
-    near[b] = m;
+    if (o == 0) near[b] = !leaf ? 0.0 : (own < m) ? m : own;
 }
 
 // Transfer of phi to a new tree.  Copy: new box b takes the old box src[b]
@@ -2352,12 +2374,12 @@ void launch_face_xt(const int32_t *nbr, const int32_t *cfslot, int64_t n, int32_
 void launch_refine_near(const int32_t *n27, const int32_t *isleaf, const double *scores, int64_t n, double *near,
                         hipStream_t s) {
     if (n <= 0) return;
-    hipLaunchKernelGGL(k_refine_near, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n27, isleaf, scores, n,
+    hipLaunchKernelGGL(k_refine_near, dim3((unsigned)((n + 7) / 8)), dim3(256), 0, s, n27, isleaf, scores, n,
                        near);
 }
 void launch_refine_scores(const Geo &g, const double *rhs, int64_t n, double *scores, hipStream_t s) {
     if (n <= 0) return;
-    hipLaunchKernelGGL(k_refine_scores, dim3((unsigned)xcd_grid(n)), dim3(256), 0, s, g, rhs, n, scores);
+    hipLaunchKernelGGL(k_refine_scores, dim3((unsigned)xcd_grid((n + 3) / 4)), dim3(256), 0, s, g, rhs, n, scores);
 }
 void launch_transfer_copy(const double *from, double *to, const int32_t *src, int64_t n, hipStream_t s) {
     if (n <= 0) return;

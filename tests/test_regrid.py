@@ -314,6 +314,30 @@ def test_gpu_scores_match_numpy():
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("boxes", [uniform_boxes(1), uniform_boxes(2), refine_boxes_explicit(2, [(2, 1, 0, 1)]),
+                                   refine_boxes_explicit(3, [(3, 1, 2, 3), (3, 0, 0, 0), (4, 2, 4, 7)])],
+                         ids=lambda b: str(b.n))
+def test_gpu_scores_and_near_on_partial_workgroups(boxes):
+    """The scores kernel takes 4 boxes a workgroup and the near kernel 8: box
+    counts around those sizes, with a NaN cell in every box (skipped, as by
+    fmax) and equal and zero scores among the values."""
+    g = M.Tree(boxes.level, boxes.ijk, boxes.tree)
+    rng = np.random.default_rng(boxes.n)
+    rhs = np.round(rng.lognormal(0.0, 2.0, (g.n, 8, 8, 8)), 1) * rng.choice([-1.0, 1.0], (g.n, 8, 8, 8))
+    rhs[::3] = 0.0
+    bad = rng.integers(0, 8, (g.n, 3))
+    want_rhs = rhs.copy()
+    for b, (k, j, i) in enumerate(bad):
+        rhs[b, k, j, i], want_rhs[b, k, j, i] = np.nan, 0.0
+    g.set_field(M.MG_FIELD_RHS, rhs)
+    lv, ij, tr = g.index(M.MG_IDX_LEVEL), g.index(M.MG_IDX_IJK), g.index(M.MG_IDX_TREE)
+    print("scores and near", g.n, "boxes", flush=True)
+    sc = g.refine_scores()
+    assert np.array_equal(sc, numpy_scores(lv, ij, want_rhs))
+    assert np.array_equal(g.refine_near(), near_of(lv, ij, tr, sc))
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("case", ["streamer_small", "forest"])
 def test_gpu_near_values_match_the_host_rule(case):
     """mg_refine_near on the GPU against the rule's per-box values computed
