@@ -466,7 +466,8 @@ int mg_timing_read(mg_tree *t, mg_kernel_timing_t *out);
  * solver state is unchanged.  schedule (host, [n_levels], may be NULL)
  * receives the chosen variant per level (index level-1); mg_set_schedule
  * applies a stored schedule (e.g. from a cache keyed by the tree's level
- * sizes) and rejects entries outside 0..MG_GSRB_VARIANTS-1.  All variants
+ * sizes) and rejects entries outside 0..MG_GSRB_VARIANTS-1.  A tree starts
+ * with variants chosen by the number of boxes of each level.  All variants
  * compute the same values.
  */
 #define MG_GSRB_VARIANTS 14

@@ -119,6 +119,25 @@ void give_event(mg_tree *t, hipEvent_t e) {
     if (e) t->ev_pool.push_back((void *)e);
 }
 
+// Schedule of a tree that is not tuned (a mesh that lives for a few solves):
+// by the boxes of the level.  Small levels are bound by launches, and a
+// fused sweep is one launch instead of two and also forms the level's FAS
+// right-hand side; large ones by HBM, where half-sweeps reach the copy rate,
+// need no prolongation pass, and in FP32 gain from octets (half the ghost
+// loads).  Whole FP64 solves, fused up to that level against half-sweeps
+// everywhere: 64 boxes 593 : 654 us; 320 boxes 1203 : 1396; 1792 boxes 3435 :
+// 3967; but 4016 boxes 10624 : 10549 (against the same with that level in
+// half-sweeps) and 4128 boxes 6155 : 5814, so the line lies between 1792 and
+// 4016.  FP32 above it: octets 9356, one-box half-sweeps 9603 us.
+constexpr int64_t kFusedMaxBoxes = 3000;
+void default_schedule(mg_tree *t) {
+    for (int l = 2; l <= t->nlev; l++) {
+        const bool fused = lcount(t, l) <= kFusedMaxBoxes;
+        t->sched[0][l] = fused ? kGsrbFusedVariant + 1 : kGsrbDefault;
+        t->sched[1][l] = fused ? kGsrbFusedVariant + 1 : kGsrbOctVariant + 1;
+    }
+}
+
 // ---- steps of the cycle
 // fas_first: the level's coarse FAS right-hand side is still to be formed
 // (fas_down deferred it); the first pair of fused sweeps forms it.
@@ -1072,6 +1091,7 @@ int mg_tree_create(mg_tree **out, const mg_domain *dom, int64_t n, const int32_t
         delete t;
         return rc;
     }
+    default_schedule(t);
     *out = t;
     return MG_OK;
 }

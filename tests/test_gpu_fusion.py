@@ -14,7 +14,7 @@ import numpy as np
 import pytest
 
 from paper_1708_08434_amd import mg as M
-from workloads import c1, streamer_small, refine_boxes_explicit
+from workloads import c1, streamer_small, refine_boxes_explicit, uniform_boxes
 from tests import _geom as G
 
 pytestmark = pytest.mark.gpu
@@ -102,6 +102,22 @@ def test_fusion_gives_the_same_bits(name, kind):
     assert st_got == st_ref, (st_got, st_ref)
     for q, (a, b) in enumerate(zip(got, ref)):
         assert np.array_equal(a, b), (name, kind, q, np.abs(a - b).max())
+
+
+def test_default_schedule_gives_the_half_sweeps_bits():
+    """The schedule a tree starts with (by level size: 512 and 4096 boxes lie
+    on either side of its line) against half-sweeps on every level."""
+    bl = uniform_boxes(5)
+    g = M.Tree(bl.level, bl.ijk, bl.tree, bc_type=(0, 0, 1, 0, 0, 0), bc_val=(0, 0, 0, 0, 0, 1.0))
+    g.set_field(M.MG_FIELD_RHS, np.random.default_rng(4).standard_normal((g.n, 8, 8, 8)) * 100.0)
+    say("default schedule", g.n, "boxes")
+    got = []
+    for _ in range(2):
+        for prec in (M.MG_FP64, M.MG_MIXED):
+            got.append((g.fmg_solve(precision=prec)["n_vcycles"], g.get_field(M.MG_FIELD_PHI)))
+            M.mg_set_schedule(g.h, prec, [3] * g.nlev)
+    for (k0, a), (k1, b) in zip(got[:2], got[2:]):
+        assert k0 == k1 and np.array_equal(a, b)
 
 
 def test_fusion_flags_are_checked():
