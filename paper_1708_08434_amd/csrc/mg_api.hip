@@ -126,10 +126,11 @@ void give_event(mg_tree *t, hipEvent_t e) {
 // need no prolongation pass, and in FP32 gain from octets (half the ghost
 // loads).  Whole FP64 solves, fused up to that level against half-sweeps
 // everywhere: 64 boxes 593 : 654 us; 320 boxes 1203 : 1396; 1792 boxes 3435 :
-// 3967; but 4016 boxes 10624 : 10549 (against the same with that level in
-// half-sweeps) and 4128 boxes 6155 : 5814, so the line lies between 1792 and
-// 4016.  FP32 above it: octets 9356, one-box half-sweeps 9603 us.
-constexpr int64_t kFusedMaxBoxes = 3000;
+// 3967; but, against the same with that level in half-sweeps, 2400 boxes
+// 36979 : 36930, 4016 boxes 10624 : 10549 and 4128 boxes 6155 : 5814, so the
+// line lies between 1792 and 2400.  FP32 above it: octets 9356, one-box
+// half-sweeps 9603 us.
+constexpr int64_t kFusedMaxBoxes = 2200;
 void default_schedule(mg_tree *t) {
     for (int l = 2; l <= t->nlev; l++) {
         const bool fused = lcount(t, l) <= kFusedMaxBoxes;
