@@ -148,8 +148,12 @@ void launch_efield(const Geo &g, const double *phi, const double *chat, int64_t 
                    double *e_norm, hipStream_t s);
 void launch_copy16(const void *src, void *dst, int64_t n16, int blocks, hipStream_t s);
 constexpr int kReduceChunk = 2048;  // leaf positions per first-stage block of the norm reduction
+// chunks of a tree up to which one launch does both stages: at 8 (16384 leaf
+// boxes) it walks two rounds of four chunks, about the time of two launches
+constexpr int kReduceOneMax = 8;
+// maxchunk: the most chunks of one tree; result: pinned host memory
 void launch_reduce_trees(const double *partial, const int32_t *leaf_tree, const int32_t *chunk,
-                         int64_t nchunk, const int32_t *choff, int ntree, double *part2,
+                         int64_t nchunk, int maxchunk, const int32_t *choff, int ntree, double *part2,
                          double *result, hipStream_t s);
 
 // Fluid model (fluid.hip).  Transport table of n entries (mu, D, alpha) at
@@ -170,7 +174,7 @@ struct FluidArgs {
     double dt, wa, wb;
     double *oute, *outi, *rhs;                     // rhs: the solver's colour-split field
     double *cf;                                    // [nslot][4][64] scratch
-    double *partial, *result;                      // [nleaf] scratch, [1] the time-step bound
+    double *partial, *result;                      // [nleaf] scratch, [1] the time-step bound (pinned host memory)
 };
 // One stage: restriction of ne into covered cells, the refinement-boundary
 // faces, the update of every leaf box and the minimum time-step bound.

@@ -2101,13 +2101,21 @@ __global__ __launch_bounds__(256) void k_ir_update(double *__restrict__ phi, con
 }
 
 // Per-tree reduction of the per-box partials in a fixed order, in two
-// stages.  Stage 1: block c sums the partials of the leaf boxes at positions
+// stages.  Stage 1 sums the partials of chunk c, the leaf boxes at positions
 // leaf_tree[chunk[c].begin .. chunk[c].end) (a range of one tree, at most
-// kReduceChunk long) into part2[c].  Stage 2: block t sums the chunks
-// choff[t] .. choff[t+1] of tree t into result[2t] (sum) and result[2t+1]
-// (max).
-__device__ __forceinline__ void block_sum_max(double &s, double &m, double *S, double *M) {
-    int t = threadIdx.x;
+// kReduceChunk long).  Stage 2 sums the chunks choff[t] .. choff[t+1] of tree
+// t into result[2t] (sum) and result[2t+1] (max).  result is pinned host
+// memory: after a stream synchronisation the host reads it, with no copy.
+//
+// Where no tree has more than kReduceOneMax chunks, one launch does both
+// stages (k_reduce_one, one workgroup per tree, four chunks at a time);
+// larger trees spread their chunks over workgroups and sum them in a second
+// launch.  Either way every sum is taken in the same order, so the results
+// are the same bits.  A check on the uniform 32^3 grid spent 4.4 us on each
+// of two reductions and 4.1 us on the copy, the price of three launches.
+
+// Sum and max over the 256 threads t of a group (S, M: the group's 256).
+__device__ __forceinline__ void block_sum_max(int t, double &s, double &m, double *S, double *M) {
     S[t] = s;
     M[t] = m;
     __syncthreads();
@@ -2121,6 +2129,16 @@ __device__ __forceinline__ void block_sum_max(double &s, double &m, double *S, d
     s = S[0];
     m = M[0];
 }
+// This thread's share of chunk c
+__device__ __forceinline__ void chunk_part(const double *__restrict__ partial, const int32_t *__restrict__ leaf_tree,
+                                           const int32_t *__restrict__ chunk, int c, int t, double &s, double &m) {
+    const int end = chunk[3 * c + 2];
+    for (int q = chunk[3 * c + 1] + t; q < end; q += 256) {
+        int64_t p = leaf_tree[q];
+        s += partial[2 * p];
+        m = nanmax(partial[2 * p + 1], m);
+    }
+}
 
 __global__ __launch_bounds__(256) void k_reduce_chunks(const double *__restrict__ partial,
                                                        const int32_t *__restrict__ leaf_tree,
@@ -2128,14 +2146,9 @@ __global__ __launch_bounds__(256) void k_reduce_chunks(const double *__restrict_
                                                        double *__restrict__ part2) {
     __shared__ double S[256], M[256];
     int c = blockIdx.x, t = threadIdx.x;
-    int beg = chunk[3 * c + 1], end = chunk[3 * c + 2];
     double s = 0.0, m = 0.0;
-    for (int q = beg + t; q < end; q += 256) {
-        int64_t p = leaf_tree[q];
-        s += partial[2 * p];
-        m = nanmax(partial[2 * p + 1], m);
-    }
-    block_sum_max(s, m, S, M);
+    chunk_part(partial, leaf_tree, chunk, c, t, s, m);
+    block_sum_max(t, s, m, S, M);
     if (t == 0) {
         part2[2 * c] = s;
         part2[2 * c + 1] = m;
@@ -2152,8 +2165,38 @@ __global__ __launch_bounds__(256) void k_reduce_trees(const double *__restrict__
         s += part2[2 * c];
         m = nanmax(part2[2 * c + 1], m);
     }
-    block_sum_max(s, m, S, M);
+    block_sum_max(t, s, m, S, M);
     if (t == 0) {
+        result[2 * tr] = s;
+        result[2 * tr + 1] = m;
+    }
+}
+
+__global__ __launch_bounds__(1024) void k_reduce_one(const double *__restrict__ partial,
+                                                     const int32_t *__restrict__ leaf_tree,
+                                                     const int32_t *__restrict__ chunk,
+                                                     const int32_t *__restrict__ choff,
+                                                     double *__restrict__ result) {
+    __shared__ double S[1024], M[1024], CS[kReduceOneMax], CM[kReduceOneMax];
+    const int tr = blockIdx.x, t = threadIdx.x & 255, g = threadIdx.x >> 8;
+    const int c0 = choff[tr], nc = choff[tr + 1] - c0;
+    for (int p = 0; p < nc; p += 4) {  // block-uniform
+        double s = 0.0, m = 0.0;
+        if (p + g < nc) chunk_part(partial, leaf_tree, chunk, c0 + p + g, t, s, m);
+        block_sum_max(t, s, m, S + 256 * g, M + 256 * g);
+        if (t == 0 && p + g < nc) {
+            CS[p + g] = s;
+            CM[p + g] = m;
+        }
+        __syncthreads();
+    }
+    double s = 0.0, m = 0.0;
+    if (t < nc) {
+        s += CS[t];
+        m = nanmax(CM[t], m);
+    }
+    block_sum_max(t, s, m, S + 256 * g, M + 256 * g);
+    if (threadIdx.x == 0) {
         result[2 * tr] = s;
         result[2 * tr + 1] = m;
     }
@@ -2401,11 +2444,14 @@ void launch_copy16(const void *src, void *dst, int64_t n16, int blocks, hipStrea
                        n16);
 }
 void launch_reduce_trees(const double *partial, const int32_t *leaf_tree, const int32_t *chunk,
-                         int64_t nchunk, const int32_t *choff, int ntree, double *part2,
+                         int64_t nchunk, int maxchunk, const int32_t *choff, int ntree, double *part2,
                          double *result, hipStream_t s) {
-    if (nchunk > 0)
-        hipLaunchKernelGGL(k_reduce_chunks, dim3((unsigned)nchunk), dim3(256), 0, s, partial, leaf_tree,
-                           chunk, part2);
+    if (maxchunk <= kReduceOneMax) {
+        hipLaunchKernelGGL(k_reduce_one, dim3((unsigned)ntree), dim3(1024), 0, s, partial, leaf_tree, chunk, choff,
+                           result);
+        return;
+    }
+    hipLaunchKernelGGL(k_reduce_chunks, dim3((unsigned)nchunk), dim3(256), 0, s, partial, leaf_tree, chunk, part2);
     hipLaunchKernelGGL(k_reduce_trees, dim3((unsigned)ntree), dim3(256), 0, s, part2, choff, result);
 }
 

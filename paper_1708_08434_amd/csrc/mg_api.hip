@@ -414,8 +414,8 @@ template <typename T> void fmg_pass(mg_tree *t, const Fields<T> &F, int nd, int 
         int top = std::min(low - 1, t->nlev);
         launch_box_norms(f64(t).g, t->d.phi, t->d.rhs, t->d.chat, t->d.leaf, 0, t->fstart[top + 1],
                          t->d.partial, nullptr, stream_of(t));
-        launch_reduce_trees(t->d.partial, t->d.leaf_tree, t->d.chunk, (int64_t)t->chunk.size() / 3, t->d.choff,
-                            t->ntree, t->d.part2, t->d.result + beff_slot, stream_of(t));
+        launch_reduce_trees(t->d.partial, t->d.leaf_tree, t->d.chunk, (int64_t)t->chunk.size() / 3, t->maxchunk,
+                            t->d.choff, t->ntree, t->d.part2, t->d.result + beff_slot, stream_of(t));
     }
     if (one) {
         bottom(t, F, nd, nu, true, t->nlev >= low);  // fas_down(2), coarse, prolong(2), V-cycle(2)
@@ -450,20 +450,18 @@ void norms_launch(mg_tree *t, int slot, float *r32) {
     Fields<double> F = f64(t);
     ensure_cf_all(t, F);
     launch_box_norms(F.g, F.phi, F.rhs, F.chat, t->d.leaf, 0, t->nleaf, t->d.partial, r32, stream_of(t));
-    launch_reduce_trees(t->d.partial, t->d.leaf_tree, t->d.chunk, (int64_t)t->chunk.size() / 3, t->d.choff,
-                        t->ntree, t->d.part2, t->d.result + slot, stream_of(t));
+    launch_reduce_trees(t->d.partial, t->d.leaf_tree, t->d.chunk, (int64_t)t->chunk.size() / 3, t->maxchunk,
+                        t->d.choff, t->ntree, t->d.part2, t->d.result + slot, stream_of(t));
 }
 
-int read_results(mg_tree *t, int count) {
-    int rc = hip_check(hipMemcpyAsync(t->host_result, t->d.result, count * sizeof(double),
-                                      hipMemcpyDeviceToHost, (hipStream_t)t->stream), "norm readback");
-    if (rc) return rc;
+// The reductions write host_result themselves: wait for them.
+int read_results(mg_tree *t) {
     return hip_check(hipStreamSynchronize((hipStream_t)t->stream), "stream synchronize");
 }
 
 int norms(mg_tree *t) {
     norms_launch(t, 0, nullptr);
-    return read_results(t, 2 * t->ntree);
+    return read_results(t);
 }
 
 // Per-tree norm of the residual of phi = 0 (boundary data folded in), into
@@ -592,10 +590,10 @@ int record(mg_tree *t, mg_tree::Graph &g, int seq, int nd, int nu) {
 }
 
 // Run a sequence (replaying its graph when enabled and the host-side state
-// matches the recorded one), then read back count result values.  Timing
+// matches the recorded one), then wait for its norms (read).  Timing
 // probes need events on the bound stream between launches, so the timing
 // mode always launches kernel by kernel.
-int run_seq(mg_tree *t, int seq, const mg_solve_opts *o, int count) {
+int run_seq(mg_tree *t, int seq, const mg_solve_opts *o, bool read) {
     int nd = o->n_down, nu = o->n_up;
     mg_tree::Graph &g = t->graphs[seq];
     bool use = o->graphs && !t->timing;
@@ -611,12 +609,12 @@ int run_seq(mg_tree *t, int seq, const mg_solve_opts *o, int count) {
     }
     if (!use) {
         run_body(t, seq, nd, nu);
-        return count ? read_results(t, count) : MG_OK;
+        return read ? read_results(t) : MG_OK;
     }
     int rc = hip_check(hipGraphLaunch((hipGraphExec_t)g.exec, (hipStream_t)t->stream), "graph launch");
     if (rc) return rc;
     load_state(t, g.post);
-    return count ? read_results(t, count) : MG_OK;
+    return read ? read_results(t) : MG_OK;
 }
 
 // Turn the per-tree norms in host_result[0..2T) into statistics.  A forest's
@@ -664,7 +662,7 @@ int iterate(mg_tree *t, const mg_solve_opts *o, mg_solve_stats *s, SeqOf seq_of)
             return MG_ENOCONV;
         }
         double prev = s->rel_res;
-        int rc = run_seq(t, seq_of(k), o, 2 * t->ntree);
+        int rc = run_seq(t, seq_of(k), o, true);
         if (rc) return rc;
         s->n_vcycles = k;
         if ((rc = record_check(t, s, k))) return rc;
@@ -686,7 +684,7 @@ int vcycles_no_stats(mg_tree *t, const mg_solve_opts *o, int n) {
     restrict_for_check(t, f64(t));
     ensure_cf_all(t, f64(t));
     int rc = MG_OK;
-    for (int k = 0; k < n && !rc; k++) rc = run_seq(t, mg_tree::SEQ_V, o, 0);
+    for (int k = 0; k < n && !rc; k++) rc = run_seq(t, mg_tree::SEQ_V, o, false);
     if (!rc) restrict_all(t, f64(t));  // every covered cell: the mean of its children
     if (!rc) rc = hip_check(hipGetLastError(), "kernel launch");
     return rc;
@@ -948,7 +946,7 @@ int learned_solve_levels(mg_tree *t, mg_nn *nn, const LearnedWs &L, const mg_sol
                          mg_learned_stats *lst) {
     const int T = t->ntree;
     double t0 = now_ms();
-    int rc = run_seq(t, mg_tree::SEQ_FMG, o, 4 * T);
+    int rc = run_seq(t, mg_tree::SEQ_FMG, o, true);
     if (rc) return s->status = rc;
     for (int tr = 0; tr < T; tr++) t->beff_tree[tr] = std::sqrt(t->host_result[2 * T + 2 * tr]);
     if ((rc = record_check(t, s, 0))) return s->status = rc;
@@ -963,7 +961,7 @@ int learned_solve_levels(mg_tree *t, mg_nn *nn, const LearnedWs &L, const mg_sol
         }
         double prev = s->rel_res;
         if (k == 1 || !use) {
-            if ((rc = run_seq(t, mg_tree::SEQ_VCHECK, o, 2 * T))) return s->status = rc;
+            if ((rc = run_seq(t, mg_tree::SEQ_VCHECK, o, true))) return s->status = rc;
         } else {
             double tl = now_ms();
             dirty_all(f32(t));
@@ -973,7 +971,7 @@ int learned_solve_levels(mg_tree *t, mg_nn *nn, const LearnedWs &L, const mg_sol
             run_body(t, mg_tree::SEQ_VCHECK, o->n_down, o->n_up);
             t->level_hook = nullptr;
             rc = t->hook_rc;
-            if (!rc) rc = read_results(t, 2 * T);
+            if (!rc) rc = read_results(t);
             if (rc) return s->status = rc;
             lst->t_learned_ms += now_ms() - tl;
         }
@@ -1292,7 +1290,6 @@ static int bind_tables(mg_tree *t, void *ws, void *stream) {
     d.chat = (double *)(base + t->off.chat);
     d.bcval = t->off.bcval >= 0 ? (double *)(base + t->off.bcval) : nullptr;
     d.partial = (double *)(base + t->off.partial);
-    d.result = (double *)(base + t->off.result);
     d.e32 = (float *)(base + t->off.e32);
     d.r32 = (float *)(base + t->off.r32);
     d.old32 = (float *)(base + t->off.old32);
@@ -1302,6 +1299,10 @@ static int bind_tables(mg_tree *t, void *ws, void *stream) {
     d.dpad = (void *)(base + t->off.dpad);
     if (!t->host_result) {
         int rc = take_pinned(4 * t->ntree * sizeof(double), &t->host_result, &t->host_result_bytes);
+        if (rc) return rc;
+    }
+    {
+        int rc = hip_check(hipHostGetDevicePointer((void **)&d.result, t->host_result, 0), "pinned buffer address");
         if (rc) return rc;
     }
     // The host-built tables fill [0, off.xt) of the workspace: staged at
@@ -1464,13 +1465,13 @@ int mg_fmg_solve(mg_tree *t, const mg_solve_opts *o, mg_solve_stats *st) {
     double t0 = now_ms();
     int T = t->ntree;
     if (o->precision == MG_FP64) {
-        if ((rc = run_seq(t, mg_tree::SEQ_FMG, o, 4 * T))) return s->status = rc;
+        if ((rc = run_seq(t, mg_tree::SEQ_FMG, o, true))) return s->status = rc;
         for (int tr = 0; tr < T; tr++) t->beff_tree[tr] = std::sqrt(t->host_result[2 * T + 2 * tr]);
         if ((rc = record_check(t, s, 0))) return s->status = rc;
         rc = iterate(t, o, s, [](int) { return (int)mg_tree::SEQ_VCHECK; });
     } else {
         // mixed precision: FP64 residual, FP32 correction cycles, FP64 update
-        if ((rc = run_seq(t, mg_tree::SEQ_MIX_START, o, 2 * T))) return s->status = rc;
+        if ((rc = run_seq(t, mg_tree::SEQ_MIX_START, o, true))) return s->status = rc;
         for (int tr = 0; tr < T; tr++) t->beff_tree[tr] = std::sqrt(t->host_result[2 * tr]);
         if ((rc = record_check(t, s, 0))) return s->status = rc;
         rc = iterate(t, o, s, [](int k) {
@@ -1512,8 +1513,8 @@ int mg_vcycle(mg_tree *t, const mg_solve_opts *o, int n_cycles, mg_solve_stats *
         for (int k = 0; k < n_cycles && k < 64; k++) s->rel_hist[k] = std::nan("");
         restrict_for_check(t, f64(t));
         ensure_cf_all(t, f64(t));
-        for (int k = 1; k < n_cycles && !rc; k++) rc = run_seq(t, mg_tree::SEQ_V, o, 0);
-        if (!rc) rc = run_seq(t, mg_tree::SEQ_VCHECK, o, 2 * t->ntree);
+        for (int k = 1; k < n_cycles && !rc; k++) rc = run_seq(t, mg_tree::SEQ_V, o, false);
+        if (!rc) rc = run_seq(t, mg_tree::SEQ_VCHECK, o, true);
         if (!rc) {
             s->n_vcycles = n_cycles;
             rc = record_check(t, s, n_cycles);
@@ -1528,13 +1529,13 @@ int mg_vcycle(mg_tree *t, const mg_solve_opts *o, int n_cycles, mg_solve_stats *
     if (o->precision != MG_FP64) {
         // the FP32 correction's right-hand side is the FP64 leaf residual
         norms_launch(t, 0, t->d.r32);
-        if ((rc = read_results(t, 2 * t->ntree))) return s->status = rc;
+        if ((rc = read_results(t))) return s->status = rc;
     }
     if (n_cycles <= 0) {
         rc = iterate(t, o, s, [seq](int) { return seq; });
     } else {
         for (int k = 1; k <= n_cycles && !rc; k++) {
-            if ((rc = run_seq(t, seq, o, 2 * t->ntree))) break;
+            if ((rc = run_seq(t, seq, o, true))) break;
             s->n_vcycles = k;
             rc = record_check(t, s, k);
         }
@@ -1653,7 +1654,6 @@ void fluid_layout(const mg_tree *t, int32_t ntab, decltype(mg_tree::foff) &o) {
     o.cfrev = take(t->n * 24 * (int64_t)sizeof(int32_t));
     o.cf = take(t->nslot * 256 * (int64_t)sizeof(double));
     o.part = take(t->nleaf * (int64_t)sizeof(double));
-    o.res = take(sizeof(double));
     o.n0e = take(cells);
     o.n0i = take(cells);
     o.n1e = take(cells);
@@ -1702,13 +1702,11 @@ int fluid_stage(mg_tree *t, const double *ef, const double *en, double *ne, cons
     A.rhs = t->d.rhs;
     A.cf = fdp(t, t->foff.cf);
     A.partial = fdp(t, t->foff.part);
-    A.result = fdp(t, t->foff.res);
+    A.result = t->d.result;
     launch_fluid_stage(geo(t, false), A, s);
     int rc = hip_check(hipGetLastError(), "fluid stage launch");
     if (rc || !lim) return rc;
-    rc = hip_check(hipMemcpyAsync(t->host_result, A.result, sizeof(double), hipMemcpyDeviceToHost, s),
-                   "fluid time-step bound copy");
-    if (!rc) rc = hip_check(hipStreamSynchronize(s), "fluid stage");
+    rc = hip_check(hipStreamSynchronize(s), "fluid stage");
     if (!rc) *lim = t->host_result[0];
     return rc;
 }
@@ -2402,7 +2400,7 @@ int mg_learned_solve(mg_tree *t, mg_nn *nn, void *ws, int64_t ws_bytes, const mg
     const int T = t->ntree;
     Fields<double> F = f64(t);
     const size_t bytes = (size_t)t->n * 512 * sizeof(double);
-    if ((rc = run_seq(t, mg_tree::SEQ_FMG, o, 4 * T))) return s->status = rc;
+    if ((rc = run_seq(t, mg_tree::SEQ_FMG, o, true))) return s->status = rc;
     for (int tr = 0; tr < T; tr++) t->beff_tree[tr] = std::sqrt(t->host_result[2 * T + 2 * tr]);
     if ((rc = record_check(t, s, 0))) return s->status = rc;
     bool use = true;
@@ -2413,7 +2411,7 @@ int mg_learned_solve(mg_tree *t, mg_nn *nn, void *ws, int64_t ws_bytes, const mg
             return s->status = MG_ENOCONV;
         }
         double prev = s->rel_res;
-        if ((rc = run_seq(t, mg_tree::SEQ_VCHECK, o, 2 * T))) return s->status = rc;
+        if ((rc = run_seq(t, mg_tree::SEQ_VCHECK, o, true))) return s->status = rc;
         s->n_vcycles = k;
         if ((rc = record_check(t, s, k))) return s->status = rc;
         if (s->rel_res > o->rel_tol && use) {

@@ -89,7 +89,8 @@ struct DevTables {
     double *chat = nullptr;      // [nslot][64] tangentially interpolated coarse values
     double *bcval = nullptr;     // [n][6][64] or null
     double *partial = nullptr;   // [n_leaf][2] per-box residual sums
-    double *result = nullptr;    // [4*ntree] per-tree (sum r^2 h^3, max |r|), then the same for phi = 0
+    double *result = nullptr;    // [4*ntree] per-tree (sum r^2 h^3, max |r|), then the same for phi = 0:
+                                 // host_result as the device addresses it
     // FP32 correction fields of the mixed-precision solve (same layouts)
     float *e32 = nullptr;        // correction
     float *r32 = nullptr;        // its right-hand side (FP64 residual rounded, FAS data)
@@ -125,18 +126,19 @@ struct mg_tree {
     bool bottom_ok = false;                             // levels 1-2 can run as one launch
     std::vector<int32_t> leaf_tree, tree_off;           // leaf positions grouped by tree
     std::vector<int32_t> chunk, choff;                  // norm-reduction chunks (tree, begin, end)
+    int maxchunk = 0;                                   // most chunks of one tree
     int64_t sstart[mg::kMaxLevel + 2] = {0};            // slots of level l: [sstart[l], sstart[l+1])
     int64_t nslot = 0, nleaf = 0;
     mg_domain dom{};
     double eig[3 * 64 + 3 * 8] = {0};
     // ---- workspace layout (byte offsets) ----
     struct { int64_t nbr, cfslot, cfq, xt, n27, slotx, ijk, parent, refined, leaf, cleaf, oldcp, leafpos, cmask, slots, leaf_tree, tree_off, chunk, choff, part2, isleaf, tid, root2, eig,
-             phi, rhs, old, chat, bcval, partial, result, e32, r32, old32, chat32, swp, fas, dpad, total; } off{};
+             phi, rhs, old, chat, bcval, partial, e32, r32, old32, chat32, swp, fas, dpad, total; } off{};
     // ---- fluid model (mg_fluid_bind): caller's second workspace ----
     void *fws = nullptr;
     int32_t ntab = 0;
     double emax = 0.0;
-    struct { int64_t tab, cfrev, cf, part, res, n0e, n0i, n1e, n1i, ef, en, total; } foff{};
+    struct { int64_t tab, cfrev, cf, part, n0e, n0i, n1e, n1i, ef, en, total; } foff{};
     // ---- bound device state ----
     void *ws = nullptr;
     void *stream = nullptr;      // caller's stream: every replay and direct launch goes here

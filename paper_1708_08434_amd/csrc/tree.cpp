@@ -461,6 +461,7 @@ int build_tree(mg_tree *t, const mg_domain *dom, int64_t n, const int32_t *level
             t->chunk.push_back(std::min<int32_t>(b + kReduceChunk, t->tree_off[tr + 1]));
         }
         t->choff[tr + 1] = (int32_t)(t->chunk.size() / 3);
+        t->maxchunk = std::max(t->maxchunk, t->choff[tr + 1] - t->choff[tr]);
     }
     // first level-2 box of each tree (its 8 children of the root, in octant
     // order), or -1 for a tree that is a single root box; the one-launch
@@ -508,7 +509,6 @@ int build_tree(mg_tree *t, const mg_domain *dom, int64_t n, const int32_t *level
     t->off.chat = take(8 * 64 * t->nslot);
     t->off.bcval = dom->per_cell_bc ? take(8 * 6 * 64 * n) : -1;
     t->off.partial = take(16 * t->nleaf);
-    t->off.result = take(8 * 4 * (int64_t)ntree);
     t->off.e32 = take(4 * kCells * n);
     t->off.r32 = take(4 * kCells * n);
     t->off.old32 = take(4 * kCells * n);
