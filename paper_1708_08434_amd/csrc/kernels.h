@@ -9,7 +9,8 @@ namespace mg {
 // Read-only geometry shared by the stencil kernels.
 struct Geo {
     const int32_t *nbr;     // [n][6]
-    const int32_t *cfslot;  // [n][6]
+    const int32_t *cfslot;  // [n][6] slot of a refinement-boundary face; else -1, or -2 where
+                            // the same-level neighbour has children
     const int32_t *cfq;     // [n][6]
     const int32_t *xt;      // [n][6][4][2] faces of the face neighbours
     const int32_t *n27;     // [n][27] same-level box at ijk + o, o in {-1,0,1}^3 (x fastest);

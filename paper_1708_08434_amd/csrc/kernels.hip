@@ -528,14 +528,23 @@ __global__ __launch_bounds__(512) void k_gsrb_oct(Geo g, T *__restrict__ phi, co
 // neighbours' face layers, so each box recomputes the 6 x 32 red cells of its
 // same-level face neighbours that touch its black face cells, with the red
 // update's own arithmetic on the old field (a red cell reads only black cells
-// and ghosts).  Their inputs are staged in LDS once: the neighbour's adjacent
-// layer of black cells (which are also the ghosts of this box's red face
-// cells), its second layer under the recomputed cells, their right-hand
-// side, and the ghosts of the recomputed cells on the neighbour's edges.  One
-// launch per sweep instead of two, with the same 24 B per cell plus the
-// neighbours' face layers.  256 threads per box; thread t owns red cell t
-// and black cell 256 + t (colour-split order), and for t < 192 face entry t:
-// face d = t / 32, position q = t % 32 in the layer.
+// and ghosts).  One launch per sweep instead of two, with the same 24 B per
+// cell plus the neighbours' face layers.  256 threads per box; thread t owns
+// red cell t and black cell 256 + t (colour-split order), and in waves 0-2 one
+// red and one black face cell of axis t / 64.
+//
+// What a thread does besides 7 FP64 operations a cell is finding addresses, so
+// that is kept small: the box and its surroundings sit in LDS as one padded
+// grid, cells -2..9 of each axis, colour-split like a box (rows of 6), where
+// every ghost is stored in the cell that it stands for, so the six neighbours
+// of a cell are at constant offsets from its own place; a wave holds the face
+// entries of one axis, so that the axis is a scalar; a load reads one
+// neighbour, from a scalar base; and all loads are issued before the first
+// wait.  With the neighbours found by selects among the box and separate ghost
+// arrays, and offsets per lane, a sweep of 64 boxes took 5.17 us, of 14224
+// boxes 40.8 and of 187984 boxes 630 (FP64; FP32 4.92, 35.2 and 505); now 4.03,
+// 34 and 540 (3.81, 25 and 400), against 6.2, 44.5 and 525 (5.9, 27.7 and 325)
+// for two half-sweeps.
 //
 // The first sweep after a restriction can also complete the coarse
 // right-hand side of the full approximation scheme (the values k_fas_rhs
@@ -546,6 +555,33 @@ __global__ __launch_bounds__(512) void k_gsrb_oct(Geo g, T *__restrict__ phi, co
 // plus that cell's old value.  fas = 2 (the next sweep) reads those values
 // from fasbuf and copies a box's own back into rhs; nothing reads rhs of a
 // box with children meanwhile, so the copy races with no read.
+
+// Places in the padded grid: red cells (i + j + k even) from 0, black from
+// kSwC, the ghosts of the recomputed cells across the neighbour's tangential
+// faces (6 faces x 4 edges x 4 cells: a place of the grid would have to hold
+// two of them) from kSwE, and a FAS sweep's old red cells from kSwO.
+constexpr int kSwC = 12 * 12 * 6, kSwE = 2 * kSwC, kSwO = kSwE + 96;
+// Cell (layer, u, v) of a face of axis A (u, v along the tangential axes): its
+// offset within a colour of a box, and its place in the grid within a colour.
+template <int A> __device__ __forceinline__ int face_off(int layer, int u, int v) {
+    return A == 0 ? v * 32 + u * 4 + (layer >> 1) : A == 1 ? v * 32 + layer * 4 + (u >> 1) : layer * 32 + v * 4 + (u >> 1);
+}
+template <int A> __device__ __forceinline__ int face_place(int layer, int u, int v) {
+    return A == 0   ? (v + 2) * 72 + (u + 2) * 6 + ((layer + 2) >> 1)
+           : A == 1 ? (v + 2) * 72 + (layer + 2) * 6 + ((u + 2) >> 1)
+                    : (layer + 2) * 72 + (v + 2) * 6 + ((u + 2) >> 1);
+}
+// fn with the axis w (wave-uniform) as a compile-time constant
+template <int A> struct Axis { static constexpr int a = A; };
+template <typename F> __device__ __forceinline__ void with_axis(int w, F fn) {
+    if (w == 0)
+        fn(Axis<0>());
+    else if (w == 1)
+        fn(Axis<1>());
+    else
+        fn(Axis<2>());
+}
+
 template <typename T, bool FAS>
 __global__ __launch_bounds__(256) void k_gsrb_sweep(Geo g, const T *__restrict__ src,
                                                     T *__restrict__ dst, T *__restrict__ rhs,
@@ -553,26 +589,16 @@ __global__ __launch_bounds__(256) void k_gsrb_sweep(Geo g, const T *__restrict__
                                                     int64_t nbx, T h2, int xcd, int fas,
                                                     const int32_t *__restrict__ isleaf, T inv_h2,
                                                     T *__restrict__ fasbuf) {
-    // P: red part = new red values (after the red half), black part = old
-    // black values.  HR: ghosts of the red face cells (old field).  D2, BH:
-    // second-layer black value and right-hand side of each recomputed red
-    // cell.  EG: ghosts of the recomputed cells across the neighbour's
-    // tangential faces (4 edges x 4 cells per face).  HB: per black face
-    // cell, the recomputed red value across a same-level face, the Dirichlet
-    // value at a domain face, or c_hat at a refinement boundary.  With
-    // fas = 1 on a box with children: PR, the old red values, and GB, the
-    // ghosts of the black face cells; NR, the old value of each recomputed
-    // red cell of a neighbour with children.
-    __shared__ T P[512], HR[192], D2[192], BH[192], EG[96], HB[192];
-    __shared__ T PR[FAS ? 256 : 1], GB[FAS ? 192 : 1], NR[FAS ? 192 : 1];
-    int64_t lb = xcd ? xcd_map(blockIdx.x, nbx) : (int64_t)blockIdx.x;
+    __shared__ T L[FAS ? kSwO + kSwC : kSwO];
+    const int64_t lb = xcd ? xcd_map(blockIdx.x, nbx) : (int64_t)blockIdx.x;
     if (lb >= nbx) return;
-    int64_t b = b0 + lb;
-    int t = threadIdx.x;
-    const FaceTab ft = face_tab(g, b);
+    const int64_t b = b0 + lb;
+    const int t = threadIdx.x;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);  // waves 0-2: the faces of axis w
     if (!FAS) fas = 0;
     const bool own_fas = fas != 0 && isleaf[b] == 0;
-    T ob = src[b * 512 + 256 + t];
+    const T *own = src + b * 512;
+    T ob = own[256 + t];
     T br, bb;
     if (own_fas && fas == 2) {
         br = fasbuf[b * 512 + t];
@@ -584,128 +610,147 @@ __global__ __launch_bounds__(256) void k_gsrb_sweep(Geo g, const T *__restrict__
         bb = rhs[b * 512 + 256 + t];
     }
     T orr = (T)0;
-    if (own_fas && fas == 1) orr = src[b * 512 + t];
-    // face entry of this thread (t < 192): the black face cell (ub, v) of
-    // face d, u along t1 and v along t2, at layer lx of this box
-    int fd = t >> 5, fq = t & 31, fv = fq >> 2;
-    int fa = fd >> 1, fside = fd & 1, ft1, ft2;
-    tangential(fa, ft1, ft2);
-    int flx = fside ? 7 : 0;
-    int fub = 2 * (fq & 3) + ((flx + fv + 1) & 1);
-    int fnb = t < 192 ? pick6(ft.nb, fd) : -3;
-    bool nb_fas = fas != 0 && fnb >= 0 && isleaf[fnb] == 0;
-    if (t < 192) {
-        gsrb_ghost<T>(g, ft, src, chat, b, 0, t, HR);
-        if (own_fas && fas == 1) gsrb_ghost<T>(g, ft, src, chat, b, 1, t, GB);
-        if (fnb >= 0) {
-            int c[3];
-            c[ft1] = fub;
-            c[ft2] = fv;
-            c[fa] = fside ? 1 : 6;  // neighbour's second layer
-            D2[t] = src[(int64_t)fnb * 512 + cs_idx3(c)];
-            c[fa] = fside ? 0 : 7;  // neighbour's adjacent layer: the recomputed red cell
-            if (nb_fas && fas == 2) {
-                BH[t] = fasbuf[(int64_t)fnb * 512 + cs_idx3(c)];
-            } else {
-                BH[t] = rhs[(int64_t)fnb * 512 + cs_idx3(c)];
-                if (nb_fas) NR[t] = src[(int64_t)fnb * 512 + cs_idx3(c)];
-            }
-            if (fq < 16) {
-                // edge e4 of the neighbour's layer (-t1, +t1, -t2, +t2), cell idx
-                int e4 = fq >> 2, idx = fq & 3;
-                int cu = e4 == 0 ? 0 : e4 == 1 ? 7 : 2 * idx + ((flx + (e4 == 2 ? 1 : 0)) & 1);
-                int cv = e4 == 2 ? 0 : e4 == 3 ? 7 : 2 * idx + ((flx + (e4 == 0 ? 1 : 0)) & 1);
-                int ax = e4 < 2 ? ft1 : ft2, s1, s2;
-                tangential(ax, s1, s2);
-                c[ft1] = cu;
-                c[ft2] = cv;
-                const int32_t *xt = g.xt + (b * 6 + fd) * 8;
-                EG[fd * 16 + fq] = ghost_at<T>(g, src, chat, fnb, 2 * ax + (e4 & 1), xt[2 * e4],
-                                               xt[2 * e4 + 1], c[s1], c[s2]);
-            }
-        } else if (fnb == -2) {
-            HB[t] = bc_value<T>(g, b, fd, fub, fv);
-        } else {
-            HB[t] = chat[(int64_t)pick6(ft.slot, fd) * 64 + fv * 8 + fub];
+    if (own_fas && fas == 1) orr = own[t];
+    // this thread's cells: the same place in both colours' grids
+    const int m = t & 3, j = (t >> 2) & 7, k = t >> 5;
+    const int at = ((k + 2) * 12 + j + 2) * 6 + m + 1;
+    const int odd = (j + k) & 1;  // the red cell is the row's second of the pair
+    bool cf = false;
+#pragma unroll
+    for (int d = 0; d < 6; d++) cf = cf || g.nbr[b * 6 + d] == -1;
+    // Face entries (waves 0-2, axis w): a lane holds one red face cell on side
+    // hf and one black face cell on the other side (so a load from one
+    // neighbour fills all lanes, from a scalar base), position (m, fv) of 4 x 8
+    // in the layer.  lx, lo: the two sides' layers in the box; p_red: the place
+    // of the red cell behind the black face cell.
+    const int hf = (t >> 5) & 1, fv = (t >> 2) & 7, lx = 7 * hf, lo = 7 - lx;
+    const int ur = 2 * m + ((lx + fv) & 1), ub = 2 * m + ((lo + fv + 1) & 1);
+    int p_red = 0;
+    bool same = false, slot = false, nb_fas = false;  // of the black face cell's face
+    T bh = (T)0, nr = (T)0, ch = (T)0;
+    auto load_faces = [&](auto A) __attribute__((always_inline)) {
+        constexpr int a = decltype(A)::a, t1 = a == 0 ? 1 : 0, t2 = a == 2 ? 1 : 2;
+        const int p_black = kSwC + face_place<a>(hf ? 8 : -1, ur, fv);
+        p_red = face_place<a>(hf ? -1 : 8, ub, fv);
+        // the black cell behind the red face cell and, on the other side, the
+        // red cell to recompute (n_red) and the black cell behind that
+        const int n_black = 256 + face_off<a>(lo, ur, fv), n_red = face_off<a>(lx, ub, fv);
+        const int n_second = 256 + face_off<a>(hf ? 6 : 1, ub, fv);
+        const int p_second = kSwC + face_place<a>(hf ? -2 : 9, ub, fv);
+        // all loads are issued before the first value is stored in LDS
+        const int nb0 = g.nbr[b * 6 + 2 * a], nb1 = g.nbr[b * 6 + 2 * a + 1];
+        const bool f0 = fas != 0 && g.cfslot[b * 6 + 2 * a] == -2, f1 = fas != 0 && g.cfslot[b * 6 + 2 * a + 1] == -2;
+        const int nbr_red = hf ? nb1 : nb0, nbr_black = hf ? nb0 : nb1;  // of the two face cells' faces
+        const bool edge = (t & 31) < 16 && nbr_red >= 0;
+        int2 x = make_int2(-2, -2);
+        if (edge) x = reinterpret_cast<const int2 *>(g.xt)[(b * 6 + 2 * a + hf) * 4 + ((t >> 2) & 3)];
+        T v0 = (T)0, v1 = (T)0, ev = (T)0;
+        if (nb0 >= 0) {
+            v0 = (src + (int64_t)nb0 * 512)[hf ? n_second : n_black];
+            if (hf) bh = ((f0 && fas == 2 ? fasbuf : rhs) + (int64_t)nb0 * 512)[n_red];
+            if (FAS && fas == 1 && hf) nr = (src + (int64_t)nb0 * 512)[n_red];
         }
-    }
-    P[256 + t] = ob;
-    if (own_fas && fas == 1) PR[t] = orr;
+        if (nb1 >= 0) {
+            v1 = (src + (int64_t)nb1 * 512)[hf ? n_black : n_second];
+            if (!hf) bh = ((f1 && fas == 2 ? fasbuf : rhs) + (int64_t)nb1 * 512)[n_red];
+            if (FAS && fas == 1 && !hf) nr = (src + (int64_t)nb1 * 512)[n_red];
+        }
+        same = nbr_black >= 0;
+        slot = nbr_black == -1;
+        nb_fas = hf ? f0 : f1;
+        if (edge) {
+            // edge e4 (-t1, +t1, -t2, +t2) of the neighbour's layer, cell m
+            // along it: the black cell across the neighbour's face there
+            const int e4 = (t >> 2) & 3, end = (e4 & 1) ? 7 : 0, along = 2 * m + ((lx + 1 + (e4 & 1)) & 1);
+            auto edge_off = [=](int across) { return face_off<a>(lo, e4 < 2 ? across : along, e4 < 2 ? along : across); };
+            if (x.x >= 0) {
+                ev = src[(int64_t)x.x * 512 + 256 + edge_off(7 - end)];
+            } else {
+                const T *N = src + (int64_t)nbr_red * 512;
+                const int ef = (e4 < 2 ? 2 * t1 : 2 * t2) + (e4 & 1);
+                // the cell on that face: u, v along the layer's axis and the
+                // edge, in increasing order of axes
+                const bool first = a < (e4 < 2 ? t2 : t1);
+                const int eu = first ? lo : along, ew = first ? along : lo;
+                ev = N[edge_off(end)];
+                if (x.x == -1)
+                    ev = cf_ghost<T>(chat[(int64_t)x.y * 64 + ew * 8 + eu], ev, N[256 + edge_off((e4 & 1) ? 6 : 1)]);
+                else if (g.bct[ef] != 1)
+                    ev = dirichlet_ghost<T>(bc_value<T>(g, nbr_red, ef, eu, ew), ev);
+            }
+        }
+#pragma unroll
+        for (int side = 0; side < 2; side++) {
+            const int fd = 2 * a + side, nb = side ? nb1 : nb0;
+            const bool red = hf == side;  // this side is the red face cell's
+            if (nb >= 0) {
+                L[red ? p_black : p_second] = side ? v1 : v0;
+            } else if (nb == -2) {
+                const T v = own[red ? face_off<a>(lx, ur, fv) : 256 + face_off<a>(lo, ub, fv)];
+                const T gh = g.bct[fd] == 1 ? v : dirichlet_ghost<T>(bc_value<T>(g, b, fd, red ? ur : ub, fv), v);
+                L[red ? p_black : p_red] = gh;
+                if (FAS && !red) nr = gh;
+            } else {
+                const T c = chat[(int64_t)g.cfslot[b * 6 + fd] * 64 + fv * 8 + (red ? ur : ub)];
+                if (red)
+                    L[p_black] = cf_ghost<T>(c, own[face_off<a>(lx, ur, fv)], own[256 + face_off<a>(hf ? 6 : 1, ur, fv)]);
+                else
+                    ch = c;
+            }
+        }
+        if (FAS) L[kSwO + p_red] = nr;
+        if (edge) L[kSwE + 16 * (2 * a + hf) + (t & 15)] = ev;
+    };
+    if (w < 3) with_axis(w, load_faces);
+    L[kSwC + at] = ob;
+    if (own_fas && fas == 1) L[kSwO + at] = orr;
     __syncthreads();
-    int m = t & 3, j = (t >> 2) & 7, k = t >> 5;
-    int row = (k * 8 + j) * 4;
+    // neighbour sum of this thread's cell of the other colour than the grid R
+    auto sum = [at](const T *R, int second) __attribute__((always_inline)) {
+        const T *x = R + at - 1 + second, *y = R + at - 72;
+        return x[0] + x[1] + y[66] + y[78] + y[0] + y[144];
+    };
     if (own_fas && fas == 1) {  // black cell's right-hand side from the old field
-        int i = 2 * m + ((j + k + 1) & 1);
-        T xm = i > 0 ? PR[row + ((i - 1) >> 1)] : GB[0 * 32 + k * 4 + (j >> 1)];
-        T xp = i < 7 ? PR[row + ((i + 1) >> 1)] : GB[1 * 32 + k * 4 + (j >> 1)];
-        T ym = j > 0 ? PR[row - 4 + m] : GB[2 * 32 + k * 4 + m];
-        T yp = j < 7 ? PR[row + 4 + m] : GB[3 * 32 + k * 4 + m];
-        T zm = k > 0 ? PR[row - 32 + m] : GB[4 * 32 + j * 4 + m];
-        T zp = k < 7 ? PR[row + 32 + m] : GB[5 * 32 + j * 4 + m];
-        T s = xm + xp + ym + yp + zm + zp;
-        bb = (s - (T)6 * ob) * inv_h2 + bb;
+        bb = (sum(L + kSwO, 1 - odd) - (T)6 * ob) * inv_h2 + bb;
         fasbuf[b * 512 + 256 + t] = bb;
     }
     {  // red cell (i + j + k even)
-        int i = 2 * m + ((j + k) & 1);
-        const T *S = P + 256;
-        T xm = i > 0 ? S[row + ((i - 1) >> 1)] : HR[0 * 32 + k * 4 + (j >> 1)];
-        T xp = i < 7 ? S[row + ((i + 1) >> 1)] : HR[1 * 32 + k * 4 + (j >> 1)];
-        T ym = j > 0 ? S[row - 4 + m] : HR[2 * 32 + k * 4 + m];
-        T yp = j < 7 ? S[row + 4 + m] : HR[3 * 32 + k * 4 + m];
-        T zm = k > 0 ? S[row - 32 + m] : HR[4 * 32 + j * 4 + m];
-        T zp = k < 7 ? S[row + 32 + m] : HR[5 * 32 + j * 4 + m];
-        T s = xm + xp + ym + yp + zm + zp;
+        const T sm = sum(L + kSwC, odd);
         if (own_fas && fas == 1) {
-            br = (s - (T)6 * orr) * inv_h2 + br;
+            br = (sm - (T)6 * orr) * inv_h2 + br;
             fasbuf[b * 512 + t] = br;
         }
-        T nr = (s - h2 * br) * (T)kSixth;
-        P[t] = nr;
-        dst[b * 512 + t] = nr;
+        const T v = (sm - h2 * br) * (T)kSixth;
+        L[at] = v;
+        dst[b * 512 + t] = v;
     }
-    if (fnb >= 0) {  // recomputed red cell of the same-level neighbour
-        const T *R = HR + fd * 32;
-        const T *E = EG + fd * 16;
-        int cx[3];
-        cx[fa] = flx;
-        cx[ft1] = fub;
-        cx[ft2] = fv;
-        T toward = P[cs_idx3(cx)];  // this box's black face cell (old)
-        T away = D2[t];
-        T nm = fside ? toward : away, np = fside ? away : toward;
-        T um = fub == 0 ? E[0 + (fv >> 1)] : R[fv * 4 + ((fub - 1) >> 1)];
-        T up = fub == 7 ? E[4 + (fv >> 1)] : R[fv * 4 + ((fub + 1) >> 1)];
-        T vm = fv == 0 ? E[8 + (fub >> 1)] : R[(fv - 1) * 4 + (fub >> 1)];
-        T vp = fv == 7 ? E[12 + (fub >> 1)] : R[(fv + 1) * 4 + (fub >> 1)];
-        // axes: a = 0 -> (n, u, v); a = 1 -> (u, n, v); a = 2 -> (u, v, n)
-        T xm = fa == 0 ? nm : um, xp = fa == 0 ? np : up;
-        T ym = fa == 0 ? um : fa == 1 ? nm : vm, yp = fa == 0 ? up : fa == 1 ? np : vp;
-        T zm = fa == 2 ? nm : vm, zp = fa == 2 ? np : vp;
-        T s = xm + xp + ym + yp + zm + zp;
-        T bh = BH[t];
-        if (nb_fas && fas == 1) bh = (s - (T)6 * NR[t]) * inv_h2 + bh;
-        HB[t] = (s - h2 * bh) * (T)kSixth;
-    }
+    // recomputed red cell of the same-level neighbour: its neighbours are at
+    // constant offsets too, but for the edge ghosts at the ends of the layer
+    auto recompute = [&](auto A) __attribute__((always_inline)) {
+        constexpr int a = decltype(A)::a;
+        const T *P = L + kSwC + p_red, *X = P - 1 + (a == 0 ? hf : ub & 1), *E = L + kSwE + 32 * a + 16 * (1 - hf);
+        const T um = *(ub == 0 ? E + (fv >> 1) : a == 0 ? P - 6 : X);
+        const T up = *(ub == 7 ? E + 4 + (fv >> 1) : a == 0 ? P + 6 : X + 1);
+        const T vm = *(fv == 0 ? E + 8 + m : a == 2 ? P - 6 : P - 72);
+        const T vp = *(fv == 7 ? E + 12 + m : a == 2 ? P + 6 : P + 72);
+        const T nm = a == 0 ? X[0] : a == 1 ? P[-6] : P[-72], np = a == 0 ? X[1] : a == 1 ? P[6] : P[72];
+        const T sm = a == 0 ? nm + np + um + up + vm + vp : a == 1 ? um + up + nm + np + vm + vp : um + up + vm + vp + nm + np;
+        if (nb_fas && fas == 1) bh = (sm - (T)6 * nr) * inv_h2 + bh;
+        L[p_red] = (sm - h2 * bh) * (T)kSixth;
+    };
+    if (same) with_axis(w, recompute);
     __syncthreads();
-    {  // black cell: neighbours are new red values; face ghosts as in the
-       // black half-sweep (own = the old black value, inward = new red)
-        int i = 2 * m + ((j + k + 1) & 1);
-        auto face = [&](int d, T hv, T inward) -> T {
-            int nb = pick6(ft.nb, d);
-            if (nb >= 0) return hv;
-            if (nb == -2) return g.bct[d] == 1 ? ob : dirichlet_ghost<T>(hv, ob);
-            return cf_ghost<T>(hv, ob, inward);
+    if (cf) {  // block-uniform: the black ghosts at refinement boundaries read the new red cell behind
+        auto ghosts = [&](auto A) __attribute__((always_inline)) {
+            constexpr int a = decltype(A)::a;
+            L[p_red] = cf_ghost<T>(ch, L[kSwC + face_place<a>(lo, ub, fv)], L[face_place<a>(hf ? 1 : 6, ub, fv)]);
         };
-        T xm = i > 0 ? P[row + ((i - 1) >> 1)] : face(0, HB[0 * 32 + k * 4 + (j >> 1)], P[row]);
-        T xp = i < 7 ? P[row + ((i + 1) >> 1)] : face(1, HB[1 * 32 + k * 4 + (j >> 1)], P[row + 3]);
-        T ym = j > 0 ? P[row - 4 + m] : face(2, HB[2 * 32 + k * 4 + m], P[row + 4 + m]);
-        T yp = j < 7 ? P[row + 4 + m] : face(3, HB[3 * 32 + k * 4 + m], P[row - 4 + m]);
-        T zm = k > 0 ? P[row - 32 + m] : face(4, HB[4 * 32 + j * 4 + m], P[row + 32 + m]);
-        T zp = k < 7 ? P[row + 32 + m] : face(5, HB[5 * 32 + j * 4 + m], P[row - 32 + m]);
-        T s = xm + xp + ym + yp + zm + zp;
-        dst[b * 512 + 256 + t] = (s - h2 * bb) * (T)kSixth;
+        if (slot) with_axis(w, ghosts);
+        __syncthreads();
     }
+    // black cell: its neighbours are new red values; domain ghosts as in the
+    // black half-sweep (from the old black value)
+    dst[b * 512 + 256 + t] = (sum(L, 1 - odd) - h2 * bb) * (T)kSixth;
 }
 
 // Coarse value of cell D = C + dir * e_ax (level l-1, relative to box Q),

@@ -60,7 +60,8 @@ template <typename T> class RawArray {
 // Device-side views of the workspace; all pointers are into one allocation.
 struct DevTables {
     int32_t *nbr = nullptr;      // [n][6]  face neighbour (-1 refinement boundary, -2 domain)
-    int32_t *cfslot = nullptr;   // [n][6]  slot of a refinement-boundary face, or -1
+    int32_t *cfslot = nullptr;   // [n][6]  slot of a refinement-boundary face; else -1, or -2
+                                 //         where the same-level neighbour has children
     int32_t *cfq = nullptr;      // [n][6]  coarser box across a refinement-boundary face
     int32_t *xt = nullptr;       // [n][6][4][2] faces of the face neighbours (fused sweep)
     int32_t *n27 = nullptr;      // [n][27] same-level box at ijk + o (-1 coarser, -2 outside)

@@ -341,8 +341,13 @@ int build_tree(mg_tree *t, const mg_domain *dom, int64_t n, const int32_t *level
         }
     }
     });
-    // refinement-boundary face slots, grouped by level
+    // refinement-boundary face slots, grouped by level; on the other faces
+    // the entry says whether the same-level neighbour has children (-2)
     t->cfslot.assign(6 * n, -1);
+    parallel_for(n, [&](int64_t lo, int64_t hi) {
+        for (int64_t q = 6 * lo; q < 6 * hi; q++)
+            if (t->nbr[q] >= 0 && t->child[8 * (int64_t)t->nbr[q]] >= 0) t->cfslot[q] = -2;
+    });
     t->slots.clear();
     for (int l = 1; l <= kMaxLevel + 1; l++) {
         t->sstart[l] = (int64_t)t->slots.size() / 2;
