@@ -1435,47 +1435,49 @@ __global__ __launch_bounds__(512) void k_coarse(Geo g, T *__restrict__ phi, cons
 // exact solve, prolongation of the correction and the up-sweeps.  Level 2 of
 // a tree is empty or all 8 children of the root (Morton = octant order from
 // root2[tree]), i.e. one uniform 16^3 grid whose only ghosts are domain
-// ghosts; it is held in LDS (colour-split, rows x fastest) with its
-// right-hand side, the doubled Dirichlet values of its six faces and the
-// root's fields (natural order), so the ~20 dependent steps cost a
-// workgroup barrier each instead of a launch each.  The arithmetic of every
-// cell, and the order of every sum, are those of k_gsrb, k_resid_restrict,
-// k_fas_rhs, k_coarse and k_prolong_cf.  fmg != 0 first runs the FMG pass's
-// own bottom (restriction, root solve, prolongation, without smoothing).
-
+// ghosts, so the ~20 dependent steps cost a workgroup barrier each instead of
+// a launch each.  The arithmetic of every cell, and the order of every sum,
+// are those of k_gsrb, k_resid_restrict, k_fas_rhs, k_coarse and k_prolong_cf.
+// fmg != 0 first runs the FMG pass's own bottom (restriction, root solve,
+// prolongation, without smoothing).
+//
+// One workgroup has one CU, so issuing instructions bounds it.  A thread owns
+// the cells (I, J, K0 .. K0+3), two of each colour, with their values and
+// right-hand sides in registers; the grid sits in LDS with a ghost layer,
+// where each owner keeps its cells' domain ghosts up to date, so a cell's
+// neighbours along x and y are at constant offsets, and along z three of four
+// are the thread's own.  With both colours of the grid in LDS, ghosts formed
+// by selects and all places computed anew, a V(2,2) bottom took 19.3 us (FP32
+// 17.5); now 14.9 (12.7), of which 1.3 a sweep.
+// Domain data of one axis of a cell: whether it lies at the axis' lower or
+// upper face, and that face's ghost as sgn own + off (Dirichlet 2 g - own,
+// Neumann own; 0 and 0 inside).  g is the face value at (u, v) of box b.
+template <typename T> struct BotFace {
+    int at;  // -1, +1 or 0: the side
+    double g;
+    T sgn, off;
+};
 template <typename T>
-__device__ __forceinline__ T root_ghost(const Geo &g, int64_t r, int d, int u, int v, T own) {
-    if (g.bct[d] == 1) return own;
-    return dirichlet_ghost<T>(bc_value<T>(g, r, d, u, v), own);
+__device__ __forceinline__ BotFace<T> bot_face(const Geo &geo, int64_t b, int axis, bool lower, bool upper, int u,
+                                               int v) {
+    BotFace<T> f;
+    // (values selected, not places: a selected place would put geo in scratch)
+    const int c0 = geo.bct[2 * axis], c1 = geo.bct[2 * axis + 1];
+    const double g0 = geo.bcv[2 * axis], g1 = geo.bcv[2 * axis + 1];
+    const bool neumann = (upper ? c1 : c0) == 1;
+    f.at = lower ? -1 : upper ? 1 : 0;
+    f.g = upper ? g1 : g0;
+    if (geo.bcval && f.at) f.g = geo.bcval[(b * 6 + 2 * axis + (upper ? 1 : 0)) * 64 + v * 8 + u];
+    f.sgn = neumann ? (T)1 : (T)-1;
+    f.off = neumann ? (T)0 : (T)2 * (T)f.g;
+    if (neumann || !f.at) f.g = 0.0;
+    return f;
 }
-// The 16^3 grid in LDS is colour-split like a box: colour (I+J+K)&1, then
-// row K*16 + J, then I/2, so a wave of a half-sweep reads consecutive words.
-__device__ __forceinline__ int cs16(int I, int J, int K) {
-    return (((I + J + K) & 1) << 11) + ((K * 16 + J) << 3) + (I >> 1);
-}
-// (I, J, K) of colour-split index p of the 16^3 grid
-__device__ __forceinline__ void cs16_cell(int p, int &I, int &J, int &K) {
-    J = (p >> 3) & 15;
-    K = (p >> 7) & 15;
-    I = 2 * (p & 7) + ((J + K + (p >> 11)) & 1);
-}
-// six-neighbour sum of fine cell (I, J, K), order -x, +x, -y, +y, -z, +z.
-// Domain ghosts: own (Neumann) or GB - own with GB = 2 g (Dirichlet), GB
-// indexed by the face cell (v * 16 + u, u and v along the tangential axes in
-// increasing order).
-template <typename T>
-__device__ __forceinline__ T bot_sum(const T *F2, const T *GB, const int nm[6], int I, int J, int K,
-                                     T own) {
-    const T *S = F2 + ((((I + J + K) & 1) ^ 1) << 11);  // the other colour
-    int row = (K * 16 + J) << 3;
-    T xm = I > 0 ? S[row + ((I - 1) >> 1)] : nm[0] ? own : GB[0 * 256 + K * 16 + J] - own;
-    T xp = I < 15 ? S[row + ((I + 1) >> 1)] : nm[1] ? own : GB[1 * 256 + K * 16 + J] - own;
-    T ym = J > 0 ? S[row - 8 + (I >> 1)] : nm[2] ? own : GB[2 * 256 + K * 16 + I] - own;
-    T yp = J < 15 ? S[row + 8 + (I >> 1)] : nm[3] ? own : GB[3 * 256 + K * 16 + I] - own;
-    T zm = K > 0 ? S[row - 128 + (I >> 1)] : nm[4] ? own : GB[4 * 256 + J * 16 + I] - own;
-    T zp = K < 15 ? S[row + 128 + (I >> 1)] : nm[5] ? own : GB[5 * 256 + J * 16 + I] - own;
-    return xm + xp + ym + yp + zm + zp;
-}
+// Place of cell (I, J, K), each -1..16, of the 16^3 grid with its ghost layer:
+// rows of 18, planes padded to a multiple of 32 (the two planes that a wave
+// of one colour reads then address the same LDS banks in turn)
+constexpr int kBotRow = 18, kBotPlane = 352, kBotGrid = 18 * kBotPlane;
+__device__ __forceinline__ int bot_at(int I, int J, int K) { return (K + 1) * kBotPlane + (J + 1) * kBotRow + I + 1; }
 // colour-split index c of a box -> (i, j, k)
 __device__ __forceinline__ void cs_cell(int c, int &i, int &j, int &k) {
     int q = c & 255;
@@ -1491,11 +1493,10 @@ __global__ __launch_bounds__(1024) void k_bottom(Geo g, T *__restrict__ phi, T *
                                                  T h2_2, T inv_h2_2, T inv_h2_1, double h1, int nd,
                                                  int nu, int fmg, int fas2,
                                                  const int32_t *__restrict__ isleaf) {
-    // F2, B2: level-2 field and right-hand side; GB: 2 g on the six faces of
-    // the 16^3 grid; F1, B1, O1: the root's phi, rhs, old; W: the level-2
-    // residual, then the root solve's X and Y, then the root correction
-    // padded by its domain ghosts (10^3).
-    __shared__ T F2[4096], B2[4096], GB[6 * 256], F1[512], B1[512], O1[512];
+    // F2: level-2 field with its ghost layer; F1, B1, O1: the root's phi, rhs,
+    // old; W: the level-2 residual, then the root solve's X and Y, then the
+    // root correction padded by its domain ghosts (10^3).
+    __shared__ T F2[kBotGrid], F1[512], B1[512], O1[512];
     __shared__ double W[4096], V[192], L[24];
     T *R2 = reinterpret_cast<T *>(W);
     double *X = W, *Y = W + 512;
@@ -1504,11 +1505,51 @@ __global__ __launch_bounds__(1024) void k_bottom(Geo g, T *__restrict__ phi, T *
     const int64_t r = r0 + blockIdx.x;
     const int64_t first2 = root2[blockIdx.x];
     const bool has2 = first2 >= 0;
-    int nm[6];
-#pragma unroll
-    for (int d = 0; d < 6; d++) nm[d] = g.bct[d] == 1;
     // root cell of this thread (tid < 512), natural order
     const int ri = tid & 7, rj = (tid >> 3) & 7, rk = (tid >> 6) & 7;
+    // this thread's run of cells (I, J, K0 + q), q = 0..3; its cells of colour
+    // c are q = pc and pc + 2 with pc = (I + J + c) & 1, and f[c], b[c] hold
+    // them.  at: place of q = 0.
+    const int I = tid & 15, J = (tid >> 4) & 15, K0 = 4 * (tid >> 8), odd = (I + J) & 1;
+    const int at = bot_at(I, J, K0);
+    const int64_t box = first2 + ((I >> 3) | ((J >> 3) << 1) | ((K0 >> 3) << 2));
+    T f[2][2], b[2][2];
+    // offset in the level's fields of cell n of colour c
+    auto cell = [&](int c, int n) __attribute__((always_inline)) {
+        return box * 512 + c * 256 + (((K0 & 7) + (odd ^ c) + 2 * n) * 8 + (J & 7)) * 4 + ((I & 7) >> 1);
+    };
+    // the root cell's domain faces
+    const BotFace<T> rx = bot_face<T>(g, r, 0, ri == 0, ri == 7, rj, rk), ry = bot_face<T>(g, r, 1, rj == 0, rj == 7, ri, rk),
+                     rz = bot_face<T>(g, r, 2, rk == 0, rk == 7, ri, rj);
+    const double tx = 2.0 * rx.g / (h1 * h1), ty = 2.0 * ry.g / (h1 * h1), tz = 2.0 * rz.g / (h1 * h1);
+    // this thread's place in the padded root correction (tid < 1000): the
+    // root cell it takes, 0 on edges and corners, and its sign in the domain
+    // ghosts
+    const int px = tid % 10 - 1, py = (tid / 10) % 10 - 1, pz = tid / 100 - 1;
+    const int pout = (px < 0 || px > 7) + (py < 0 || py > 7) + (pz < 0 || pz > 7);
+    const int pq = min(max(px, 0), 7) + 8 * min(max(py, 0), 7) + 64 * min(max(pz, 0), 7);
+    const int c0 = g.bct[0], c1 = g.bct[1], c2 = g.bct[2], c3 = g.bct[3], c4 = g.bct[4], c5 = g.bct[5];
+    const int pbc = px < 0 ? c0 : px > 7 ? c1 : py < 0 ? c2 : py > 7 ? c3 : pz < 0 ? c4 : pz > 7 ? c5 : 1;
+    // the run's: along x and y per cell (they differ in g alone), along z of
+    // the run's first or last cell
+    T gx[2][2], gy[2][2];
+    int dx = 0, dy = 0;
+    T sx = (T)0, sy = (T)0;
+    const BotFace<T> fz = bot_face<T>(g, has2 ? box : r, 2, K0 == 0, K0 == 12, I & 7, J & 7);
+#pragma unroll
+    for (int c = 0; c < 2; c++)
+#pragma unroll
+        for (int n = 0; n < 2; n++) {
+            const int k = (K0 & 7) + (odd ^ c) + 2 * n;
+            const BotFace<T> fx = bot_face<T>(g, has2 ? box : r, 0, I == 0, I == 15, J & 7, k);
+            const BotFace<T> fy = bot_face<T>(g, has2 ? box : r, 1, J == 0, J == 15, I & 7, k);
+            gx[c][n] = fx.off;
+            gy[c][n] = fy.off;
+            dx = fx.at;
+            dy = fy.at * kBotRow;
+            sx = fx.sgn;
+            sy = fy.sgn;
+        }
     if (tid < 192) V[tid] = eig[tid];
     if (tid < 24) L[tid] = eig[192 + tid];
     if (tid < 512) {
@@ -1517,62 +1558,86 @@ __global__ __launch_bounds__(1024) void k_bottom(Geo g, T *__restrict__ phi, T *
         F1[i + 8 * j + 64 * k] = phi[r * 512 + tid];
         B1[i + 8 * j + 64 * k] = rhs[r * 512 + tid];
     }
+    // stores cell n of colour c and its domain ghosts
+    auto put = [&](int c, int n) __attribute__((always_inline)) {
+        const int q = (odd ^ c) + 2 * n, p = at + q * kBotPlane;
+        const T v = f[c][n];
+        F2[p] = v;
+        if (dx) F2[p + dx] = sx * v + gx[c][n];
+        if (dy) F2[p + dy] = sy * v + gy[c][n];
+        if (K0 == 0 && q == 0) F2[p - kBotPlane] = fz.sgn * v + fz.off;
+        if (K0 == 12 && q == 3) F2[p + kBotPlane] = fz.sgn * v + fz.off;
+    };
     if (has2) {
+        // in the order of the fields (read by runs, each load would touch four
+        // times the cache lines), then handed to the owners through LDS
 #pragma unroll
         for (int w = 0; w < 4; w++) {
             int e = tid + 1024 * w, o = e >> 9, i, j, k;
             cs_cell(e & 511, i, j, k);
-            int p = cs16(8 * (o & 1) + i, 8 * ((o >> 1) & 1) + j, 8 * (o >> 2) + k);
-            F2[p] = phi[first2 * 512 + e];
-            B2[p] = rhs[first2 * 512 + e];
-        }
-        for (int e = tid; e < 6 * 256; e += 1024) {
-            int d = e >> 8, u = e & 15, v = (e >> 4) & 15, a = d >> 1, side = d & 1;
-            int c[3];  // the face cell's box: octant side along a, u and v across it
-            c[a] = side;
-            c[a == 0 ? 1 : 0] = u >> 3;
-            c[a == 2 ? 1 : 2] = v >> 3;
-            int o = c[0] | (c[1] << 1) | (c[2] << 2);
-            GB[e] = (T)2 * bc_value<T>(g, first2 + o, d, u & 7, v & 7);
+            i += 8 * (o & 1);
+            j += 8 * ((o >> 1) & 1);
+            k += 8 * (o >> 2);
+            F2[bot_at(i, j, k)] = phi[first2 * 512 + e];
+            R2[k * 256 + j * 16 + i] = rhs[first2 * 512 + e];
         }
     }
     __syncthreads();
+    if (has2) {
+#pragma unroll
+        for (int c = 0; c < 2; c++)
+#pragma unroll
+            for (int n = 0; n < 2; n++) {
+                const int q = (odd ^ c) + 2 * n;
+                f[c][n] = F2[at + q * kBotPlane];
+                b[c][n] = R2[(K0 + q) * 256 + J * 16 + I];
+                put(c, n);
+            }
+    }
+    __syncthreads();
+    // six-neighbour sums of the run's two cells of colour c, order -x, +x, -y,
+    // +y, -z, +z
+    auto sums = [&](int c, T s[2]) __attribute__((always_inline)) {
+        const int pc = odd ^ c;
+        const T *p = F2 + at + pc * kBotPlane;
+        const T e = F2[at + (pc ? 4 : -1) * kBotPlane];  // the cell beyond the run, or its ghost
+        const T o0 = f[1 - c][0], o1 = f[1 - c][1];
+        const T zm0 = pc ? o0 : e, zp0 = pc ? o1 : o0, zm1 = pc ? o1 : o0, zp1 = pc ? e : o1;
+        s[0] = p[-1] + p[1] + p[-kBotRow] + p[kBotRow] + zm0 + zp0;
+        p += 2 * kBotPlane;
+        s[1] = p[-1] + p[1] + p[-kBotRow] + p[kBotRow] + zm1 + zp1;
+    };
     // FAS right-hand side of the level-2 boxes with children, L phi + rhs
     // (the level-3 restriction has just written both), as k_fas_rhs forms
     // it: same neighbour order, same domain ghosts; stored for the rest of
     // the cycle
-    if (fas2 && has2) {
+    if (fas2 && has2 && !isleaf[box]) {
 #pragma unroll
-        for (int w = 0; w < 4; w++) {
-            int e = tid + 1024 * w, o = e >> 9, i, j, k;
-            if (isleaf[first2 + o]) continue;
-            cs_cell(e & 511, i, j, k);
-            int I = 8 * (o & 1) + i, J = 8 * ((o >> 1) & 1) + j, K = 8 * (o >> 2) + k;
-            int p = cs16(I, J, K);
-            T own = F2[p];
-            T s = bot_sum<T>(F2, GB, nm, I, J, K, own);
-            T bn = (s - (T)6 * own) * inv_h2_2 + B2[p];
-            B2[p] = bn;
-            rhs[first2 * 512 + e] = bn;
+        for (int c = 0; c < 2; c++) {
+            T s[2];
+            sums(c, s);
+#pragma unroll
+            for (int n = 0; n < 2; n++) {
+                b[c][n] = (s[n] - (T)6 * f[c][n]) * inv_h2_2 + b[c][n];
+                rhs[cell(c, n)] = b[c][n];
+            }
         }
-        __syncthreads();
     }
+    __syncthreads();  // the sums above read cells that the first half-sweep writes
 
-    auto half_sweep = [&](int C) __attribute__((always_inline)) {
-#pragma unroll
-        for (int w = 0; w < 2; w++) {
-            int p = (C << 11) + tid + 1024 * w, I, J, K;
-            cs16_cell(p, I, J, K);
-            T s = bot_sum<T>(F2, GB, nm, I, J, K, F2[p]);
-            F2[p] = (s - h2_2 * B2[p]) * (T)kSixth;
-        }
-        __syncthreads();
-    };
     auto smooth = [&](int n) __attribute__((always_inline)) {
-        for (int it = 0; it < n; it++) {
-            half_sweep(0);
-            half_sweep(1);
-        }
+        for (int it = 0; it < n; it++)
+#pragma unroll
+            for (int c = 0; c < 2; c++) {
+                T s[2];
+                sums(c, s);
+#pragma unroll
+                for (int m = 0; m < 2; m++) {
+                    f[c][m] = (s[m] - h2_2 * b[c][m]) * (T)kSixth;
+                    put(c, m);
+                }
+                __syncthreads();
+            }
     };
     // residual of level 2, restriction to the root, FAS right-hand side of
     // the root; a leaf root only copies phi -> old
@@ -1583,25 +1648,25 @@ __global__ __launch_bounds__(1024) void k_bottom(Geo g, T *__restrict__ phi, T *
             return;
         }
 #pragma unroll
-        for (int w = 0; w < 4; w++) {
-            int p = tid + 1024 * w, I, J, K;
-            cs16_cell(p, I, J, K);
-            T own = F2[p];
-            T sum = bot_sum<T>(F2, GB, nm, I, J, K, own);
-            R2[p] = resid_of<T>(B2[p], sum, own, inv_h2_2);
+        for (int c = 0; c < 2; c++) {
+            T s[2];
+            sums(c, s);
+#pragma unroll
+            for (int n = 0; n < 2; n++)
+                R2[(K0 + (odd ^ c) + 2 * n) * 256 + J * 16 + I] = resid_of<T>(b[c][n], s[n], f[c][n], inv_h2_2);
         }
         __syncthreads();
         if (tid < 512) {
             T sphi = 0, sres = 0;
+            const T *pf = F2 + bot_at(2 * ri, 2 * rj, 2 * rk), *pr = R2 + 512 * rk + 32 * rj + 2 * ri;
 #pragma unroll
             for (int dk = 0; dk < 2; dk++)
 #pragma unroll
                 for (int dj = 0; dj < 2; dj++)
 #pragma unroll
                     for (int di = 0; di < 2; di++) {
-                        int p = cs16(2 * ri + di, 2 * rj + dj, 2 * rk + dk);
-                        sphi += F2[p];
-                        sres += R2[p];
+                        sphi += pf[dk * kBotPlane + dj * kBotRow + di];
+                        sres += pr[dk * 256 + dj * 16 + di];
                     }
             T mphi = (T)0.125 * sphi;
             F1[tid] = mphi;
@@ -1611,12 +1676,10 @@ __global__ __launch_bounds__(1024) void k_bottom(Geo g, T *__restrict__ phi, T *
         __syncthreads();
         if (tid < 512) {
             T own = F1[tid];
-            T xm = ri > 0 ? F1[tid - 1] : root_ghost<T>(g, r, 0, rj, rk, own);
-            T xp = ri < 7 ? F1[tid + 1] : root_ghost<T>(g, r, 1, rj, rk, own);
-            T ym = rj > 0 ? F1[tid - 8] : root_ghost<T>(g, r, 2, ri, rk, own);
-            T yp = rj < 7 ? F1[tid + 8] : root_ghost<T>(g, r, 3, ri, rk, own);
-            T zm = rk > 0 ? F1[tid - 64] : root_ghost<T>(g, r, 4, ri, rj, own);
-            T zp = rk < 7 ? F1[tid + 64] : root_ghost<T>(g, r, 5, ri, rj, own);
+            const T hx = rx.sgn * own + rx.off, hy = ry.sgn * own + ry.off, hz = rz.sgn * own + rz.off;
+            T xm = rx.at < 0 ? hx : F1[tid - 1], xp = rx.at > 0 ? hx : F1[tid + 1];
+            T ym = ry.at < 0 ? hy : F1[tid - 8], yp = ry.at > 0 ? hy : F1[tid + 8];
+            T zm = rz.at < 0 ? hz : F1[tid - 64], zp = rz.at > 0 ? hz : F1[tid + 64];
             T s = xm + xp + ym + yp + zm + zp;
             B1[tid] = (s - (T)6 * own) * inv_h2_1 + B1[tid];
         }
@@ -1627,17 +1690,9 @@ __global__ __launch_bounds__(1024) void k_bottom(Geo g, T *__restrict__ phi, T *
         const int t = tid & 511, i = ri, j = rj, k = rk;
         if (tid < 512) {
             double rr = (double)B1[t];
-#pragma unroll
-            for (int d = 0; d < 6; d++) {
-                int a = d >> 1, sd = d & 1;
-                int ca = a == 0 ? i : a == 1 ? j : k;
-                int u = a == 0 ? j : i, v = a == 2 ? j : k;  // coordinates along the tangential axes
-                bool edge = sd ? (ca == 7) : (ca == 0);
-                if (edge && g.bct[d] == 0) {
-                    double gv = g.bcval ? g.bcval[(r * 6 + d) * 64 + v * 8 + u] : g.bcv[d];
-                    rr -= 2.0 * gv / (h1 * h1);
-                }
-            }
+            rr -= tx;
+            rr -= ty;
+            rr -= tz;
             X[t] = rr;
         }
         __syncthreads();
@@ -1668,23 +1723,20 @@ __global__ __launch_bounds__(1024) void k_bottom(Geo g, T *__restrict__ phi, T *
     auto prolong = [&]() __attribute__((always_inline)) {
         if (!has2) return;
         if (tid < 1000) {
-            int x = tid % 10 - 1, y = (tid / 10) % 10 - 1, z = tid / 100 - 1;
-            int face = x < 0 ? 0 : x > 7 ? 1 : y < 0 ? 2 : y > 7 ? 3 : z < 0 ? 4 : z > 7 ? 5 : -1;
-            int out = (x < 0 || x > 7) + (y < 0 || y > 7) + (z < 0 || z > 7);
-            int q = min(max(x, 0), 7) + 8 * min(max(y, 0), 7) + 64 * min(max(z, 0), 7);
-            T din = F1[q] - O1[q];
-            D1[tid] = out > 1 ? (T)0 : face < 0 ? din : nm[face] ? din : -din;
+            T din = F1[pq] - O1[pq];
+            D1[tid] = pout > 1 ? (T)0 : pbc == 1 ? din : -din;
         }
         __syncthreads();
 #pragma unroll
-        for (int w = 0; w < 4; w++) {
-            int p = tid + 1024 * w, I, J, K;
-            cs16_cell(p, I, J, K);
-            int c = ((K >> 1) + 1) * 100 + ((J >> 1) + 1) * 10 + (I >> 1) + 1;
-            int sx = (I & 1) ? 1 : -1, sy = (J & 1) ? 10 : -10, sz = (K & 1) ? 100 : -100;
-            T d0 = D1[c], dx = D1[c + sx], dy = D1[c + sy], dz = D1[c + sz];
-            F2[p] += (T)0.25 * d0 + (T)0.25 * (dx + dy + dz);
-        }
+        for (int c = 0; c < 2; c++)
+#pragma unroll
+            for (int n = 0; n < 2; n++) {
+                const int K = K0 + (odd ^ c) + 2 * n;
+                const T *d = D1 + ((K >> 1) + 1) * 100 + ((J >> 1) + 1) * 10 + (I >> 1) + 1;
+                T d0 = d[0], dx1 = d[(I & 1) ? 1 : -1], dy1 = d[(J & 1) ? 10 : -10], dz1 = d[(K & 1) ? 100 : -100];
+                f[c][n] += (T)0.25 * d0 + (T)0.25 * (dx1 + dy1 + dz1);
+                put(c, n);
+            }
         __syncthreads();
     };
 
@@ -1712,8 +1764,7 @@ __global__ __launch_bounds__(1024) void k_bottom(Geo g, T *__restrict__ phi, T *
         for (int w = 0; w < 4; w++) {
             int e = tid + 1024 * w, o = e >> 9, i, j, k;
             cs_cell(e & 511, i, j, k);
-            int p = cs16(8 * (o & 1) + i, 8 * ((o >> 1) & 1) + j, 8 * (o >> 2) + k);
-            phi[first2 * 512 + e] = F2[p];
+            phi[first2 * 512 + e] = F2[bot_at(8 * (o & 1) + i, 8 * ((o >> 1) & 1) + j, 8 * (o >> 2) + k)];
         }
     }
 }

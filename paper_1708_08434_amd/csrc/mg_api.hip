@@ -124,13 +124,12 @@ void give_event(mg_tree *t, hipEvent_t e) {
 // fused sweep is one launch instead of two and also forms the level's FAS
 // right-hand side; large ones by HBM, where half-sweeps reach the copy rate,
 // need no prolongation pass, and in FP32 gain from octets (half the ghost
-// loads).  Whole FP64 solves, fused up to that level against half-sweeps
-// everywhere: 64 boxes 593 : 654 us; 320 boxes 1203 : 1396; 1792 boxes 3435 :
-// 3967; but, against the same with that level in half-sweeps, 2400 boxes
-// 36979 : 36930, 4016 boxes 10624 : 10549 and 4128 boxes 6155 : 5814, so the
-// line lies between 1792 and 2400.  FP32 above it: octets 9356, one-box
-// half-sweeps 9603 us.
-constexpr int64_t kFusedMaxBoxes = 2200;
+// loads).  Whole FP64 solves with fused sweeps up to that level, against the
+// same with that level in half-sweeps: 1024 boxes and below 3246 : 3910 us, 1792
+// boxes 3151 : 3246, 4960 boxes 3096 : 3141; but 5216 boxes 5843 : 5732 and 5888
+// boxes 36663 : 36608, so the line lies at 5000.  FP32 above it: octets 9220,
+// one-box half-sweeps 9450 us.
+constexpr int64_t kFusedMaxBoxes = 5000;
 void default_schedule(mg_tree *t) {
     for (int l = 2; l <= t->nlev; l++) {
         const bool fused = lcount(t, l) <= kFusedMaxBoxes;
