@@ -1633,7 +1633,10 @@ __global__ __launch_bounds__(1024) void k_bottom(Geo g, T *__restrict__ phi, T *
                 sums(c, s);
 #pragma unroll
                 for (int m = 0; m < 2; m++) {
-                    f[c][m] = (s[m] - h2_2 * b[c][m]) * (T)kSixth;
+                    // (written as the fused multiply-add that the other kernels'
+                    // s - h2 b becomes: h2 b is constant here, and taken out
+                    // of the loop it would round on its own)
+                    f[c][m] = fmadd(-h2_2, b[c][m], s[m]) * (T)kSixth;
                     put(c, m);
                 }
                 __syncthreads();

@@ -120,6 +120,24 @@ def test_default_schedule_gives_the_half_sweeps_bits():
         assert k0 == k1 and np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("prec", [M.MG_FP64, M.MG_MIXED])
+def test_schedules_agree_where_h_is_no_power_of_two(prec):
+    """Step by step in half-sweeps against the one-launch bottom with fused
+    sweeps, half-sweeps and octets, on a domain of length 0.04: there h^2 b
+    and the sums round, so a kernel that contracts its multiply-adds in
+    another way than the others gives other bits."""
+    b = streamer_small().boxes
+    g = M.Tree(b.level, b.ijk, b.tree, length=0.04, bc_type=(1, 1, 1, 1, 0, 0), bc_val=(0, 0, 0, 0, 0, 80e3))
+    g.set_field(M.MG_FIELD_RHS, np.random.default_rng(6).standard_normal((g.n, 8, 8, 8)) * 1e11)
+    say("schedules on length 0.04", g.n, "boxes", prec)
+    got = []
+    for sch in ([0] + [3] * (g.nlev - 1), [3] * g.nlev, [3] + [7] * (g.nlev - 1), [3] + [9] * (g.nlev - 1)):
+        M.mg_set_schedule(g.h, prec, sch)
+        got.append((g.fmg_solve(precision=prec)["n_vcycles"], g.get_field(M.MG_FIELD_PHI)))
+    for k, p in got[1:]:
+        assert k == got[0][0] and np.array_equal(p, got[0][1])
+
+
 def test_fusion_flags_are_checked():
     g, _ = make_tree("streamer_small")
     with pytest.raises(M.MGError) as e:
