@@ -144,6 +144,19 @@ void launch_refine_near(const int32_t *n27, const int32_t *isleaf, const double 
 void launch_transfer_copy(const double *from, double *to, const int32_t *src, int64_t n, hipStream_t s);
 void launch_transfer_interp(const Geo &g, double *phi, const double *chat, const int32_t *list, int64_t nlist,
                             hipStream_t s);
+// The learned step's sums per range, the leaf positions of one (level, tree):
+// sums[range][9] (pinned host memory) = <r, q_{l-1}>, <r, q_l>, <r, q_{l+1}>,
+// then the six products of the three; part: [9][nchunk] scratch.  Range
+// (level - 1) * ntree + tree is the leaf positions leaf[range] .. leaf[range+1)
+// and the chunks chunk[range] .. chunk[range+1), of at most per positions.
+// With more than one tree, the two arrays (nrange + 1 entries each, leaf
+// first) are on the device at tab.
+struct LearnedRanges {
+    int32_t ntree, nrange, per;
+    int32_t leaf[17], chunk[17];
+};
+void launch_learned_sums(const Geo &g, const float *x, const float *r32, const int32_t *leaf, const int32_t *tab,
+                         const LearnedRanges &R, int nchunk, double *part, double *sums, hipStream_t s);
 // Electric field of phi on all n boxes (face components and cell strength).
 void launch_efield(const Geo &g, const double *phi, const double *chat, int64_t n, double *e_face,
                    double *e_norm, hipStream_t s);

@@ -1951,7 +1951,7 @@ __global__ __launch_bounds__(128) void k_box_norms(Geo g, const double *__restri
 
 // out[q][e] = (L x)(cell e of leaf box leaf[q]) for the composite operator
 // with the field's ghosts (same layout as the field, one 512-run per leaf
-// position); the operator applications of the learned correction step.
+// position); the operator application of the per-level learned step.
 template <typename T>
 __global__ __launch_bounds__(256) void k_leaf_apply(Geo g, const T *__restrict__ x,
                                                     const T *__restrict__ chat,
@@ -1974,6 +1974,189 @@ __global__ __launch_bounds__(256) void k_leaf_apply(Geo g, const T *__restrict__
         T own = P[c * 256 + t];
         out[q * 512 + c * 256 + t] = (sum_full<T>(P, H, i, j, k) - (T)6 * own) * inv_h2;
     }
+}
+
+// The sums of the learned step's least squares.  x holds the correction c of
+// every leaf box (and its means on the covered cells that a leaf box reads),
+// and q_m = A0 c_m is the operator on the corrections of level m alone.  A
+// leaf cell of level j sees three of them: q_j through the box's own cells and
+// those of its level, q_{j-1} through the leaf cells behind a
+// refinement-boundary face, and q_{j+1} through the covered cells of refined
+// neighbours.  So the three stencil sums of a box come from one set of
+// ghosts, each filed under the level it belongs to (a refinement-boundary
+// ghost under two: next to a box with children, the coarse values it is
+// interpolated from are means of level j), and nothing is stored but the nine
+// products <r, q>, <q, q'>.  (As three passes, one per level modulo 3, each
+// with its restrictions and c_hat and writing its q, and a pass of dot
+// products, the sums took 339 us on 16164 leaf boxes;
+// this kernel takes 72, and 108 with two boxes a workgroup.)
+//
+// A workgroup sums over one chunk, at most `per` leaf positions of one (level,
+// tree), into column blockIdx.x of part[9][nchunk].
+__device__ __forceinline__ int learned_range(const LearnedRanges &R, const int32_t *__restrict__ tab, int c,
+                                             int64_t &beg, int64_t &end) {
+    int w = 0;
+    if (!tab) {
+        while (c >= R.chunk[w + 1]) w++;
+        beg = R.leaf[w] + (int64_t)(c - R.chunk[w]) * R.per;
+        end = min(beg + R.per, R.leaf[w + 1]);
+    } else {
+        const int32_t *ch = tab + R.nrange + 1;
+        for (int lo = R.nrange; lo - w > 1;) {
+            const int m = (w + lo) >> 1;
+            if (c >= ch[m])
+                w = m;
+            else
+                lo = m;
+        }
+        beg = tab[w] + (int64_t)(c - ch[w]) * R.per;
+        end = min(beg + R.per, (int64_t)tab[w + 1]);
+    }
+    return w;
+}
+__global__ __launch_bounds__(512) void k_learned_sums(Geo g, const float *__restrict__ x,
+                                                      const float *__restrict__ r32,
+                                                      const int32_t *__restrict__ leaf,
+                                                      const int32_t *__restrict__ tab, LearnedRanges R,
+                                                      double *__restrict__ part) {
+    __shared__ float P[512], H[384], X[384];
+    __shared__ double S[8][9];
+    const int t = threadIdx.x;
+    int64_t q0, q1;
+    const int l = learned_range(R, tab, blockIdx.x, q0, q1) / R.ntree + 1;
+    const double h = g.len / (8.0 * (double)(1 << (l - 1)));
+    const float inv_h2 = (float)(1.0 / (h * h));
+    // the thread's cell and (below 384) its ghost of face d = wave, at (u, v)
+    const int o = t >> 8, j = (t >> 2) & 7, k = (t >> 5) & 7, i = 2 * (t & 3) + ((j + k + o) & 1);
+    const int d = __builtin_amdgcn_readfirstlane(t >> 6), u = t & 7, v = (t >> 3) & 7;
+    const int a = d >> 1, side = d & 1;
+    double s[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    for (int64_t q = q0; q < q1; q++) {
+        const int64_t b = leaf[q];
+        const FaceTab ft = face_tab(g, b);
+        bool other = false;  // a face of another level (block-uniform)
+#pragma unroll
+        for (int f = 0; f < 6; f++) other = other || ft.nb[f] == -1 || ft.slot[f] == -2;
+        const float own = x[b * 512 + t];
+        const double r = r32[b * 512 + t];
+        float hv = 0.0f, xv = 0.0f;
+        if (d < 6) {
+            const int nb = pick6(ft.nb, d), slot = pick6(ft.slot, d);
+            if (nb == -1) {
+                int t1, t2, c[3];
+                tangential(a, t1, t2);
+                c[t1] = u;
+                c[t2] = v;
+                c[a] = side ? 7 : 0;
+                const float edge = x[b * 512 + cs_idx3(c)];
+                c[a] = side ? 6 : 1;
+                const float in = x[b * 512 + cs_idx3(c)];
+                // c_hat as in cf_face, the covered cells apart
+                const int32_t *y = g.slotx + 8 * (int64_t)slot;
+                const int64_t Q = y[0];
+                c[a] = side ? 0 : 7;
+                c[t1] = y[1] + (u >> 1);
+                c[t2] = y[2] + (v >> 1);
+                float lf = 0.875f * x[Q * 512 + cs_idx3(c)], cov = 0.0f;
+#pragma unroll
+                for (int z = 0; z < 4; z++) {
+                    const int ax = z < 2 ? t1 : t2, up = z & 1, N = y[3 + z];
+                    const float st = ((z < 2 ? u : v) & 1) == up ? 1.0f / 32.0f + 0.125f : 1.0f / 32.0f - 0.125f;
+                    const float val = st * coarse_at<float>(g, x, Q, c, ax, up ? 1 : -1, N);
+                    if (c[ax] == (up ? 7 : 0) && N >= 0 && g.cfslot[Q * 6 + 2 * ax + up] == -2)
+                        cov += val;
+                    else
+                        lf += val;
+                }
+                hv = cf_ghost<float>(cov, edge, in);
+                xv = cf_ghost<float>(lf, 0.0f, 0.0f);
+            } else {
+                const float gv = ghost_at<float>(g, x, nullptr, b, d, nb, slot, u, v);
+                hv = slot == -2 ? 0.0f : gv;
+                xv = slot == -2 ? gv : 0.0f;
+            }
+        }
+        __syncthreads();  // the previous box is done with the buffers
+        P[t] = own;
+        if (d < 6) {
+            H[t] = hv;
+            X[t] = xv;
+        }
+        __syncthreads();
+        const double qc = (sum_full<float>(P, H, i, j, k) - 6.0f * own) * inv_h2;
+        s[1] += r * qc;
+        s[6] += qc * qc;
+        if (!other) continue;
+        // the faces of the coarser (A) and of the finer level (N)
+        float A = 0.0f, N = 0.0f;
+        auto face = [&](int f, bool at, int uv) __attribute__((always_inline)) {
+            const float w = at ? X[64 * f + uv] : 0.0f;
+            if (ft.nb[f] == -1)
+                A += w;
+            else
+                N += w;
+        };
+        face(0, i == 0, k * 8 + j);
+        face(1, i == 7, k * 8 + j);
+        face(2, j == 0, k * 8 + i);
+        face(3, j == 7, k * 8 + i);
+        face(4, k == 0, j * 8 + i);
+        face(5, k == 7, j * 8 + i);
+        const double qa = A * inv_h2, qn = N * inv_h2;
+        s[0] += r * qa;
+        s[2] += r * qn;
+        s[3] += qa * qa;
+        s[4] += qa * qc;
+        s[5] += qa * qn;
+        s[7] += qc * qn;
+        s[8] += qn * qn;
+    }
+    const double vol = h * h * h;
+    // eight of the sums folded into one a lane (three exchanges halve the
+    // sums a lane holds), then over the lanes; the ninth on its own
+#pragma unroll
+    for (int m = 4; m > 0; m >>= 1) {
+        const bool hi = t & m;
+#pragma unroll
+        for (int e = 0; e < m; e++) {
+            const double give = hi ? s[e] : s[e + m];
+            s[e] = (hi ? s[e + m] : s[e]) + __shfl_xor(give, m);
+        }
+    }
+#pragma unroll
+    for (int m = 8; m < 64; m *= 2) s[0] += __shfl_xor(s[0], m);
+#pragma unroll
+    for (int m = 1; m < 64; m *= 2) s[8] += __shfl_xor(s[8], m);
+    if ((t & 63) < 9) S[t >> 6][t & 63] = (t & 63) < 8 ? s[0] : s[8];
+    __syncthreads();
+    if (t < 9) {
+        double w = 0.0;
+#pragma unroll
+        for (int m = 0; m < 8; m++) w += S[m][t];
+        part[(int64_t)t * gridDim.x + blockIdx.x] = w * vol;
+    }
+}
+// sums[range][9] (pinned host memory) <- the sums over the chunks of a range,
+// one workgroup each.
+__global__ __launch_bounds__(256) void k_learned_reduce(const double *__restrict__ part,
+                                                        const int32_t *__restrict__ tab, LearnedRanges R, int nchunk,
+                                                        double *__restrict__ sums) {
+    __shared__ double S[4];
+    const int w = blockIdx.x / 9, e = blockIdx.x % 9, t = threadIdx.x;
+    const int c0 = tab ? tab[R.nrange + 1 + w] : R.chunk[w], c1 = tab ? tab[R.nrange + 2 + w] : R.chunk[w + 1];
+    const double *__restrict__ p = part + (int64_t)e * nchunk;
+    double v = 0.0;
+    for (int c = c0 + t; c < c1; c += 2048) {
+        double z[8];
+#pragma unroll
+        for (int k = 0; k < 8; k++) z[k] = c + 256 * k < c1 ? p[c + 256 * k] : 0.0;
+#pragma unroll
+        for (int k = 0; k < 8; k++) v += z[k];
+    }
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    if ((t & 63) == 0) S[t >> 6] = v;
+    __syncthreads();
+    if (t == 0) sums[blockIdx.x] = (S[0] + S[1]) + (S[2] + S[3]);
 }
 
 // Electric field of phi (section 2.3, E = -grad phi), one box per block:
@@ -2213,30 +2396,44 @@ __global__ __launch_bounds__(256) void k_ir_update(double *__restrict__ phi, con
 // are the same bits.  A check on the uniform 32^3 grid spent 4.4 us on each
 // of two reductions and 4.1 us on the copy, the price of three launches.
 
-// Sum and max over the 256 threads t of a group (S, M: the group's 256).
+// Sum and max over the 256 threads t of a group (S, M: the group's 256), valid
+// in its thread 0: pairs 128 and 64 apart through LDS, the rest in a wavefront.
 __device__ __forceinline__ void block_sum_max(int t, double &s, double &m, double *S, double *M) {
     S[t] = s;
     M[t] = m;
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w) {
-            S[t] += S[t + w];
-            M[t] = nanmax(M[t + w], M[t]);
-        }
-        __syncthreads();
+    if (t >= 64) return;
+    s = (S[t] + S[t + 128]) + (S[t + 64] + S[t + 192]);
+    m = nanmax(nanmax(M[t + 192], M[t + 64]), nanmax(M[t + 128], M[t]));
+    for (int w = 32; w > 0; w >>= 1) {
+        s += __shfl_down(s, w);
+        m = nanmax(__shfl_down(m, w), m);
     }
-    s = S[0];
-    m = M[0];
 }
-// This thread's share of chunk c
+// This thread's share of chunk c.  All loads go out before the first sum: as
+// a loop of gather and sum, 8 chunks took a workgroup 17.6 us, now 10.2.
 __device__ __forceinline__ void chunk_part(const double *__restrict__ partial, const int32_t *__restrict__ leaf_tree,
                                            const int32_t *__restrict__ chunk, int c, int t, double &s, double &m) {
-    const int end = chunk[3 * c + 2];
-    for (int q = chunk[3 * c + 1] + t; q < end; q += 256) {
-        int64_t p = leaf_tree[q];
-        s += partial[2 * p];
-        m = nanmax(partial[2 * p + 1], m);
+    constexpr int n = kReduceChunk / 256;
+    const int beg = chunk[3 * c + 1] + t, end = chunk[3 * c + 2];
+    int p[n];
+    double v[n], x[n];
+#pragma unroll
+    for (int k = 0; k < n; k++) p[k] = beg + 256 * k < end ? leaf_tree[beg + 256 * k] : -1;
+#pragma unroll
+    for (int k = 0; k < n; k++) {
+        v[k] = x[k] = 0.0;
+        if (p[k] >= 0) {
+            v[k] = partial[2 * (int64_t)p[k]];
+            x[k] = partial[2 * (int64_t)p[k] + 1];
+        }
     }
+#pragma unroll
+    for (int k = 0; k < n; k++)
+        if (p[k] >= 0) {
+            s += v[k];
+            m = nanmax(x[k], m);
+        }
 }
 
 __global__ __launch_bounds__(256) void k_reduce_chunks(const double *__restrict__ partial,
@@ -2504,6 +2701,12 @@ void launch_leaf_apply(const Geo &g, const T *x, const T *chat, const int32_t *l
 }
 template void launch_leaf_apply<float>(const Geo &, const float *, const float *, const int32_t *,
                                        int64_t, float *, hipStream_t);
+void launch_learned_sums(const Geo &g, const float *x, const float *r32, const int32_t *leaf, const int32_t *tab,
+                         const LearnedRanges &R, int nchunk, double *part, double *sums, hipStream_t s) {
+    hipLaunchKernelGGL(k_learned_sums, dim3((unsigned)nchunk), dim3(512), 0, s, g, x, r32, leaf, tab, R, part);
+    hipLaunchKernelGGL(k_learned_reduce, dim3((unsigned)(9 * R.nrange)), dim3(256), 0, s, part, tab, R, nchunk,
+                       sums);
+}
 void launch_efield(const Geo &g, const double *phi, const double *chat, int64_t n, double *e_face,
                    double *e_norm, hipStream_t s) {
     if (n <= 0) return;

@@ -487,6 +487,7 @@ int beff_norm(mg_tree *t) {
 //                 result[2T..4T), FMG pass, restriction pass, per-tree leaf
 //                 norms into result[0..2T) (T trees).
 //  SEQ_VCHECK:    V-cycle with the finest level on top, restriction pass, norms.
+//  SEQ_VCHECK_R:  the same, with the residual's FP32 copy (learned steps).
 //  SEQ_MIX_START: phi <- 0, leaf residual (= residual of phi = 0) in FP64 with
 //                 its FP32 copy as the correction's right-hand side, norms.
 //  SEQ_MIX_FMG / SEQ_MIX_V: e <- 0, FP32 FMG pass (first refinement step) or
@@ -509,9 +510,10 @@ void run_body(mg_tree *t, int seq, int nd, int nu) {
         norms_launch(t, 0, nullptr);
         break;
     case mg_tree::SEQ_VCHECK:
+    case mg_tree::SEQ_VCHECK_R:
         vcycle(t, F, t->nlev, nd, nu, false, true);
         restrict_for_check(t, F, nu);
-        norms_launch(t, 0, nullptr);
+        norms_launch(t, 0, seq == mg_tree::SEQ_VCHECK_R ? E.rhs : nullptr);
         break;
     case mg_tree::SEQ_V:
         // a check without its norms: the next cycle starts from the state a
@@ -601,7 +603,7 @@ int run_seq(mg_tree *t, int seq, const mg_solve_opts *o, bool read) {
     // recorded graph serves every entry.  The V-cycles need the FP64 state
     // as it is and never touch the FP32 fields.
     dirty_all(f32(t));
-    if (seq != mg_tree::SEQ_VCHECK && seq != mg_tree::SEQ_V) dirty_all(f64(t));
+    if (seq != mg_tree::SEQ_VCHECK && seq != mg_tree::SEQ_VCHECK_R && seq != mg_tree::SEQ_V) dirty_all(f64(t));
     if (use && !(g.exec && g.nd == nd && g.nu == nu && same_state(t, g.pre))) {
         int rc = record(t, g, seq, nd, nu);
         if (rc) return rc;
@@ -815,49 +817,81 @@ void solve_steps(const double *G, const double *g, double *s) {
 }
 
 // One learned step on the current FP64 phi (see mg_nn.h).  The FP32
-// correction fields serve as scratch: e32 holds the correction of one level
-// class (levels = m mod 3, whose operator images do not overlap: a leaf cell
-// of level j only sees corrections of levels j-1, j, j+1), r32 the residual.
-int learned_step_impl(mg_tree *t, mg_nn *nn, const LearnedWs &L, double *steps_host) {
+// correction fields serve as scratch: e32 holds the correction, r32 the
+// residual.  have_residual: r32 holds the residual of the current phi already
+// (a check that stored it has just run).
+int learned_step_impl(mg_tree *t, mg_nn *nn, const LearnedWs &L, double *steps_host, bool have_residual) {
     Fields<double> F = f64(t);
     Fields<float> E = f32(t);
     hipStream_t s = stream_of(t);
     const int64_t nl = t->nleaf;
-    restrict_all(t, F);
-    norms_launch(t, 0, E.rhs);
+    const int S = kStepStride, T = t->ntree;
+    if (!have_residual) {
+        restrict_all(t, F);
+        norms_launch(t, 0, E.rhs);
+    }
     launch_nn_gather(E.rhs, t->d.leaf, nl, t->d.nbr, t->d.ijk, t->d.isleaf, t->dom.len, L.x, L.scale, s);
     launch_nn_forward(nn->prm, nn->pk, nl, nullptr, L.x, L.y, nullptr, nullptr, s);
-    for (int m = 0; m < 3; m++) {
-        launch_nn_scatter(L.y, L.scale, t->d.leaf, nl, t->d.ijk, m, E.phi, s);
-        dirty_all(E);
-        restrict_all(t, E);
-        for (int l = 2; l <= t->nlev; l++) ensure_cf(t, E, l);
-        launch_leaf_apply<float>(E.g, E.phi, E.chat, t->d.leaf, nl, L.q + (int64_t)m * nl * 512, s);
-    }
+    // the correction on the leaf boxes, its means on the covered cells that a
+    // leaf box or a c_hat reads (those of a stopping test)
+    launch_nn_scatter(L.y, L.scale, t->d.leaf, nl, E.phi, s);
+    restrict_for_check(t, E);
     dirty_all(E);
-    launch_nn_dots(E.rhs, L.q, t->d.leaf, nl, t->d.ijk, t->dom.len, L.partial, s);
-    std::vector<double> part((size_t)9 * nl);
-    int rc = hip_check(hipMemcpyAsync(part.data(), L.partial, part.size() * sizeof(double),
-                                      hipMemcpyDeviceToHost, s), "step sums readback");
-    if (!rc) rc = hip_check(hipStreamSynchronize(s), "stream synchronize");
-    if (rc) return rc;
-    const int S = kStepStride, T = t->ntree;
-    std::vector<double> G((size_t)T * S * S, 0.0), g((size_t)T * S, 0.0), st((size_t)T * S, 0.0);
-    for (int64_t q = 0; q < nl; q++) {
-        int64_t b = t->leaf[q];
-        int j = t->lev[b], tr = t->tid[b];
-        const double *p = &part[9 * q];
-        double *Gt = &G[(size_t)tr * S * S], *gt = &g[(size_t)tr * S];
-        gt[j - 1] += p[0];
-        gt[j] += p[1];
-        gt[j + 1] += p[2];
-        Gt[(j - 1) * S + j - 1] += p[3];
-        Gt[(j - 1) * S + j] += p[4];
-        Gt[(j - 1) * S + j + 1] += p[5];
-        Gt[j * S + j] += p[6];
-        Gt[j * S + j + 1] += p[7];
-        Gt[(j + 1) * S + j + 1] += p[8];
+    // the leaf positions of each (level, tree) and their chunks: one box per
+    // workgroup until the chip is full, then up to 8, so that nine block sums
+    // end 8 boxes (16164 boxes: 83 us with 4 a workgroup, 72 with 8, 73 with 16)
+    LearnedRanges R;
+    R.ntree = T;
+    R.nrange = T * t->nlev;
+    R.per = (int32_t)std::max<int64_t>(1, std::min<int64_t>(8, nl / 1024));
+    std::vector<int32_t> tab(2 * (R.nrange + 1));
+    int32_t *leaf0 = tab.data(), *chunk0 = leaf0 + R.nrange + 1, nchunk = 0;
+    for (int l = 1; l <= t->nlev; l++) {
+        int64_t q = t->fstart[l];
+        for (int tr = 0; tr < T; tr++) {
+            const int w = (l - 1) * T + tr;
+            leaf0[w] = (int32_t)q;
+            chunk0[w] = nchunk;
+            const int64_t q0 = q;
+            if (T == 1)
+                q = t->fstart[l + 1];
+            else
+                while (q < t->fstart[l + 1] && t->tid[t->leaf[q]] == tr) q++;
+            nchunk += (int32_t)((q - q0 + R.per - 1) / R.per);
+        }
     }
+    leaf0[R.nrange] = (int32_t)nl;
+    chunk0[R.nrange] = nchunk;
+    int32_t *d_tab = nullptr;
+    int rc = MG_OK;
+    if (T == 1) {
+        std::copy(leaf0, leaf0 + R.nrange + 1, R.leaf);
+        std::copy(chunk0, chunk0 + R.nrange + 1, R.chunk);
+    } else {  // the table goes where the steps will: they are set after the sums
+        d_tab = (int32_t *)L.steps;
+        rc = hip_check(hipMemcpyAsync(d_tab, tab.data(), tab.size() * sizeof(int32_t), hipMemcpyHostToDevice, s),
+                       "leaf ranges upload");
+        if (rc) return rc;
+    }
+    // at most one chunk a leaf box: the sums fit in the operator images' space
+    launch_learned_sums(E.g, E.phi, E.rhs, t->d.leaf, d_tab, R, nchunk, (double *)L.q, t->d.result + 4 * T, s);
+    if ((rc = hip_check(hipGetLastError(), "learned step launch"))) return rc;
+    if ((rc = hip_check(hipStreamSynchronize(s), "stream synchronize"))) return rc;
+    std::vector<double> G((size_t)T * S * S, 0.0), g((size_t)T * S, 0.0), st((size_t)T * S, 0.0);
+    for (int tr = 0; tr < T; tr++)
+        for (int j = 1; j <= t->nlev; j++) {
+            const double *p = t->host_result + 4 * T + 9 * ((size_t)(j - 1) * T + tr);
+            double *Gt = &G[(size_t)tr * S * S], *gt = &g[(size_t)tr * S];
+            gt[j - 1] += p[0];
+            gt[j] += p[1];
+            gt[j + 1] += p[2];
+            Gt[(j - 1) * S + j - 1] += p[3];
+            Gt[(j - 1) * S + j] += p[4];
+            Gt[(j - 1) * S + j + 1] += p[5];
+            Gt[j * S + j] += p[6];
+            Gt[j * S + j + 1] += p[7];
+            Gt[(j + 1) * S + j + 1] += p[8];
+        }
     for (int tr = 0; tr < T; tr++) {
         double *Gt = &G[(size_t)tr * S * S];
         for (int l = 0; l < S; l++) Gt[l] = Gt[l * S] = 0.0;  // no level 0
@@ -896,7 +930,7 @@ int learned_level_step(mg_tree *t, mg_nn *nn, const LearnedWs &L, int l, double 
     launch_leaf_norms(F.g, F.phi, F.rhs, F.chat, list, nq, L.partial, E.rhs, s);  // r in FP32
     launch_nn_gather(E.rhs, list, nq, t->d.nbr, t->d.ijk, t->d.isleaf, t->dom.len, L.x, L.scale, s);
     launch_nn_forward(nn->prm, nn->pk, nq, nullptr, L.x, L.y, nullptr, nullptr, s);
-    launch_nn_scatter(L.y, L.scale, list, nq, t->d.ijk, -1, E.phi, s);
+    launch_nn_scatter(L.y, L.scale, list, nq, E.phi, s);
     int64_t c0 = t->sstart[l], nc = t->sstart[l + 1] - c0;
     launch_fill<float>(E.chat + c0 * 64, nc * 64, 0.0f, s);  // no correction on the coarse side
     launch_leaf_apply<float>(E.g, E.phi, E.chat, list, nq, L.q, s);
@@ -1297,7 +1331,8 @@ static int bind_tables(mg_tree *t, void *ws, void *stream) {
     d.fas = (void *)(base + t->off.fas);
     d.dpad = (void *)(base + t->off.dpad);
     if (!t->host_result) {
-        int rc = take_pinned(4 * t->ntree * sizeof(double), &t->host_result, &t->host_result_bytes);
+        // the norms of a check, then the sums of a learned step
+        int rc = take_pinned((4 + 9 * kMaxLevel) * t->ntree * sizeof(double), &t->host_result, &t->host_result_bytes);
         if (rc) return rc;
     }
     {
@@ -2358,7 +2393,7 @@ int mg_learned_step(mg_tree *t, mg_nn *nn, void *ws, int64_t ws_bytes, double *s
     if (rc || (rc = require_nn(nn)) || (rc = check_learned_ws(t, ws, ws_bytes))) return rc;
     LearnedWs L;
     learned_layout(t, (char *)ws, &L);
-    return learned_step_impl(t, nn, L, steps);
+    return learned_step_impl(t, nn, L, steps, false);
 }
 
 int mg_learned_level_step(mg_tree *t, mg_nn *nn, void *ws, int64_t ws_bytes, int level, double *steps) {
@@ -2406,20 +2441,22 @@ int mg_learned_solve(mg_tree *t, mg_nn *nn, void *ws, int64_t ws_bytes, const mg
     int stall = 0;
     for (int k = 1; s->rel_res > o->rel_tol; k++) {
         if (k > o->max_cycles) {
+            restrict_all(t, F);
             set_error("no convergence within max_cycles");
             return s->status = MG_ENOCONV;
         }
         double prev = s->rel_res;
-        if ((rc = run_seq(t, mg_tree::SEQ_VCHECK, o, true))) return s->status = rc;
+        // a learned step needs the residual itself: its check stores it
+        if ((rc = run_seq(t, use ? mg_tree::SEQ_VCHECK_R : mg_tree::SEQ_VCHECK, o, true))) return s->status = rc;
         s->n_vcycles = k;
         if ((rc = record_check(t, s, k))) return s->status = rc;
         if (s->rel_res > o->rel_tol && use) {
             double tl = now_ms(), rel_v = s->rel_res;
             rc = hip_check(hipMemcpyAsync(F.old, F.phi, bytes, hipMemcpyDeviceToDevice, stream_of(t)),
                            "save phi");
-            if (!rc) rc = learned_step_impl(t, nn, L, nullptr);
+            if (!rc) rc = learned_step_impl(t, nn, L, nullptr, true);
             if (rc) return s->status = rc;
-            restrict_all(t, F);
+            restrict_for_check(t, F);
             if ((rc = norms(t))) return s->status = rc;
             mg_solve_stats trial = *s;
             int rt = record_check(t, &trial, k);
@@ -2439,6 +2476,7 @@ int mg_learned_solve(mg_tree *t, mg_nn *nn, void *ws, int64_t ws_bytes, const mg
         }
         stall = s->rel_res >= prev ? stall + 1 : 0;
         if (stall >= 3) {
+            restrict_all(t, F);
             set_error("residual stagnates");
             return s->status = MG_ENOCONV;
         }

@@ -149,7 +149,7 @@ struct mg_tree {
     mg::DevTables d;
     bool cf_valid[mg::kMaxLevel + 2] = {false};    // c_hat of the FP64 field current per level
     bool cf_valid32[mg::kMaxLevel + 2] = {false};  // same for the FP32 correction field
-    double *host_result = nullptr;  // pinned host buffer for norms, [4*ntree]
+    double *host_result = nullptr;  // pinned host buffer: norms [4*ntree], learned sums [ntree][nlev][9]
     size_t host_result_bytes = 0;    // its capacity
     std::vector<double> beff_tree, rel_tree;  // per tree: norm of the residual of phi = 0, last rel
     // ---- optional event timing of the half-sweep kernel ----
@@ -166,7 +166,7 @@ struct mg_tree {
         int nodes = 0;  // kernel launches recorded
         bool pre[2][mg::kMaxLevel + 2], post[2][mg::kMaxLevel + 2];  // c_hat validity
     };
-    enum { SEQ_FMG = 0, SEQ_VCHECK, SEQ_MIX_START, SEQ_MIX_FMG, SEQ_MIX_V, SEQ_V, SEQ_COUNT };
+    enum { SEQ_FMG = 0, SEQ_VCHECK, SEQ_VCHECK_R, SEQ_MIX_START, SEQ_MIX_FMG, SEQ_MIX_V, SEQ_V, SEQ_COUNT };
     Graph graphs[SEQ_COUNT];
     // Gauss-Seidel launch variant per level, [0] FP64, [1] FP32 (autotuner);
     // the entry of level 1 (never smoothed) selects the bottom of the cycle:

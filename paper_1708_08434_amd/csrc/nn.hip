@@ -775,57 +775,15 @@ __global__ __launch_bounds__(256) void k_nn_gather(const float *__restrict__ r32
     if (t == 0) scale[q] = sc;
 }
 
-// e32 on leaf boxes <- scale * y (levels with level % 3 == mod3, or all when
-// mod3 < 0; zero on the other leaf boxes).
+// e32 on the listed leaf boxes <- scale * y.
 __global__ __launch_bounds__(256) void k_nn_scatter(const float *__restrict__ y,
                                                     const float *__restrict__ scale,
                                                     const int32_t *__restrict__ leaf,
-                                                    const int32_t *__restrict__ ijk4, int mod3,
                                                     float *__restrict__ e32) {
     const int64_t q = blockIdx.x;
     const int64_t b = leaf[q];
-    const int l = ijk4[b * 4 + 3];
-    const bool on = mod3 < 0 || l % 3 == mod3;
     const float sc = scale[q];
-    for (int e = threadIdx.x; e < 512; e += 256)
-        e32[b * 512 + e] = on ? sc * y[q * 512 + cs_to_nat(e)] : 0.0f;
-}
-
-// Per leaf position, with j its level and Q_m the operator applied to the
-// correction of the levels = m (mod 3): the volume-weighted sums
-// <r, q_{j-1}>, <r, q_j>, <r, q_{j+1}> and the six products of the q's.
-__global__ __launch_bounds__(256) void k_nn_dots(const float *__restrict__ r32,
-                                                 const float *__restrict__ q3,
-                                                 const int32_t *__restrict__ leaf, int64_t nleaf,
-                                                 const int32_t *__restrict__ ijk4, double len,
-                                                 double *__restrict__ partial) {
-    __shared__ double S[4];
-    const int64_t q = blockIdx.x;
-    const int64_t b = leaf[q];
-    const int t = threadIdx.x;
-    const int l = ijk4[b * 4 + 3];
-    const double h = len / (8.0 * (double)(1 << (l - 1)));
-    const float *qa = q3 + (int64_t)((l + 2) % 3) * nleaf * 512 + q * 512;
-    const float *qc = q3 + (int64_t)(l % 3) * nleaf * 512 + q * 512;
-    const float *qn = q3 + (int64_t)((l + 1) % 3) * nleaf * 512 + q * 512;
-    double s[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-    for (int e = t; e < 512; e += 256) {
-        double r = r32[b * 512 + e], a = qa[e], c = qc[e], n = qn[e];
-        s[0] += r * a;
-        s[1] += r * c;
-        s[2] += r * n;
-        s[3] += a * a;
-        s[4] += a * c;
-        s[5] += a * n;
-        s[6] += c * c;
-        s[7] += c * n;
-        s[8] += n * n;
-    }
-    const double vol = h * h * h;
-    for (int k = 0; k < 9; k++) {
-        double v = block_sum256(s[k], S);
-        if (t == 0) partial[q * 9 + k] = v * vol;
-    }
+    for (int e = threadIdx.x; e < 512; e += 256) e32[b * 512 + e] = sc * y[q * 512 + cs_to_nat(e)];
 }
 
 // Per listed box: the volume-weighted sums <r, q> and <q, q> of one column
@@ -965,18 +923,10 @@ void launch_nn_gather(const float *r32, const int32_t *leaf, int64_t nleaf, cons
                        len, x, scale);
 }
 
-void launch_nn_scatter(const float *y, const float *scale, const int32_t *leaf, int64_t nleaf,
-                       const int32_t *ijk4, int mod3, float *e32, hipStream_t s) {
+void launch_nn_scatter(const float *y, const float *scale, const int32_t *leaf, int64_t nleaf, float *e32,
+                       hipStream_t s) {
     if (nleaf <= 0) return;
-    hipLaunchKernelGGL(k_nn_scatter, dim3((unsigned)nleaf), dim3(256), 0, s, y, scale, leaf, ijk4, mod3,
-                       e32);
-}
-
-void launch_nn_dots(const float *r32, const float *q3, const int32_t *leaf, int64_t nleaf,
-                    const int32_t *ijk4, double len, double *partial, hipStream_t s) {
-    if (nleaf <= 0) return;
-    hipLaunchKernelGGL(k_nn_dots, dim3((unsigned)nleaf), dim3(256), 0, s, r32, q3, leaf, nleaf, ijk4, len,
-                       partial);
+    hipLaunchKernelGGL(k_nn_scatter, dim3((unsigned)nleaf), dim3(256), 0, s, y, scale, leaf, e32);
 }
 
 void launch_nn_dots1(const float *r32, const float *q, const int32_t *list, int64_t n, const int32_t *ijk4,

@@ -276,6 +276,39 @@ def test_learned_step_parity(forest):
     assert np.abs(upd).max() > 0
 
 
+def uniform_and_corner(level):
+    """A uniform level with two boxes refined at one corner: refinement-boundary
+    faces whose coarse side has covered cells beside it."""
+    return refine_boxes_explicit(level, [(level, 0, 0, 0), (level, 1, 0, 0)])
+
+
+@pytest.mark.parametrize("case", ["chunks of one box", "chunks of several", "trees of unlike depth"])
+def test_learned_sums_ranges(case):
+    """The least-squares sums of the learned step over (level, tree) ranges:
+    one box a chunk, several boxes and a ragged last chunk, and a forest where
+    a tree has no box on most levels."""
+    say("learned sums", case)
+    if case == "chunks of one box":
+        bl = uniform_and_corner(3)
+    elif case == "chunks of several":
+        bl = uniform_and_corner(5)
+    else:
+        bl = BoxList.concat([refine_boxes_explicit(2, []), refine_boxes_explicit(2, [(2, 1, 0, 1)], tree=1),
+                             refine_boxes_explicit(2, [(2, 0, 0, 0), (3, 1, 1, 1), (3, 0, 1, 0)], tree=2)])
+    g, o = tree_pair(bl)
+    o.fmg_solve(tol=1e30)
+    o.vcycles(1, tol=0.0)
+    g.set_field(M.MG_FIELD_PHI, o.get_field(O.PHI))
+    p = rand_params(15, scale=0.5)
+    steps = NN.Learned(g).step(NN.Net(p))
+    out = N.learned_step(o, p.astype(np.float64))
+    lv, tid, leaf = o.index(O.IDX_LEVEL), o.index(O.IDX_TREE), o.leaf_mask()
+    for tr in range(o.ntree):
+        for l in np.unique(lv[leaf & (tid == tr)]):
+            a, b = steps[tr, l], out["s"][tr, l]
+            assert abs(a - b) <= STEP_REL * max(abs(b), 1e-3 * np.abs(out["s"]).max()), (tr, l, a, b)
+
+
 def test_learned_solve_zero_network_falls_back_to_plain():
     """Zero weights give a zero correction: the step is rejected at the
     first cycle and the solve is bit-identical to the plain FP64 solve."""
