@@ -16,9 +16,10 @@
 //    channels each, per instruction) and blocked along z, so that each
 //    loaded input slice serves the three output slices it reaches;
 //    activations are stored [padded cell][channel];
-//  * layer 3 first forms Q[tap][cell] = sum_c W3[c][tap] a2[c][cell] with
-//    16x16x16 MFMAs (N = taps), then y[cell] = b3 + sum_tap Q[tap][cell+tap-1],
-//    which turns the 16->1 convolution into a dense GEMM plus a 27-term sum.
+//  * layer 3 first forms Q[dk, dj][cell] = sum over di and c of W3[c][dk, dj,
+//    di] a2[c][cell + di - 1] (N = 9 kernel rows, K = 3 x 16), then y[cell] =
+//    b3 + the 9 terms Q[dk, dj][cell + (dk - 1, dj - 1)], which turns the
+//    16->1 convolution into a dense GEMM plus a 9-term sum.
 // The backward pass (training only) keeps its FP32 gradients: each is split
 // exactly into three BF16 parts for the matrix cores.
 #include <hip/hip_runtime.h>
@@ -40,7 +41,7 @@ typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kW1 = 0, kB1 = 432, kW2 = 448, kB2 = 7360, kW3 = 7376, kB3 = 7808;
-constexpr int kP1 = 0, kP2 = 512, kP3 = 512 + 18 * 512;  // offsets in the packed fragments
+constexpr int kP1 = 0, kP2 = 512;  // offsets in the packed fragments
 
 __device__ __forceinline__ uint16_t f2bf(float f) {
     uint32_t u = __float_as_uint(f);
@@ -52,7 +53,7 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
 // NaN (its payload may differ from f2bf's).  Two values per instruction.
 __device__ __forceinline__ uint16_t f2bf_hw(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 // max(z, 0) that propagates NaN (a non-finite weight must reach the output)
-__device__ __forceinline__ float relu(float z) { return !(z <= 0.0f) ? z : 0.0f; }
+__device__ __forceinline__ float relu(float z) { return __builtin_elementwise_maximum(z, 0.0f); }
 
 // offset of tap t in a 10^3 block (x fastest)
 __host__ __device__ constexpr int tap_off(int t) { return (t / 9) * 100 + ((t / 3) % 3) * 10 + t % 3; }
@@ -79,7 +80,7 @@ __device__ __forceinline__ T block_sum256(T v, T *S) {
 
 // ------------------------------------------------------------ weight packing
 // Fragments in the lane order of the MFMA B operand (lane l holds column
-// l % 16, K rows 8 (l / 16) .. +7 for 16x16x32, 4 (l / 16) .. +3 for 16x16x16).
+// l % 16, K rows 8 (l / 16) .. +7).  Layer 3's few are formed by the forward.
 // One entry a thread: 2 us (one workgroup walking all entries: 12 us).
 __global__ __launch_bounds__(256) void k_nn_pack(const float *__restrict__ prm, uint16_t *__restrict__ pk) {
     const int e = blockIdx.x * 256 + threadIdx.x;  // grid: kNnPacked / 256
@@ -87,7 +88,7 @@ __global__ __launch_bounds__(256) void k_nn_pack(const float *__restrict__ prm, 
     if (e < kP2) {
         int lane = e >> 3, q = e & 7, o = lane & 15, g = lane >> 4, t = 8 * g + q;
         if (t < 27) v = prm[kW1 + o * 27 + t];
-    } else if (e < kP3) {
+    } else {
         // fragment f = (2 dk + type) 3 + di: type 0 has kernel rows dj = 0
         // in K groups 0-1 and dj = 1 in groups 2-3, type 1 dj = 2 in
         // groups 0-1 and zeros in 2-3
@@ -95,10 +96,6 @@ __global__ __launch_bounds__(256) void k_nn_pack(const float *__restrict__ prm, 
         int dk = f / 6, type = (f / 3) & 1, di = f % 3, o = lane & 15, g = lane >> 4, ch = 8 * (g & 1) + q;
         int dj = type == 0 ? (g < 2 ? 0 : 1) : (g < 2 ? 2 : -1);
         if (dj >= 0) v = prm[kW2 + (o * 16 + ch) * 27 + (dk * 3 + dj) * 3 + di];
-    } else {
-        int e3 = e - kP3, nt = e3 >> 8, r = e3 & 255, lane = r >> 2, q = r & 3;
-        int n = lane & 15, g = lane >> 4, tap = 16 * nt + n, ch = 4 * g + q;
-        if (tap < 27) v = prm[kW3 + ch * 27 + tap];
     }
     pk[e] = f2bf(v);
 }
@@ -112,21 +109,37 @@ static_assert(kNnPacked % 256 == 0, "one thread per packed entry");
 // Persistent workgroups of 4 waves: the weight fragments stay in registers
 // while a workgroup walks over boxes q = blockIdx.x, + gridDim.x, ..., and
 // each thread prefetches its part of the next box's input during the current
-// box.  Tiles are 16 consecutive cells (two x-rows of 8), one MFMA row each.
+// box.  Tiles are 16 consecutive cells (two x-rows of 8); wave w owns the
+// tiles of y-rows (2w, 2w+1) at every z.  In layers 1 and 2 a tile's cells are
+// the columns of the product, so that a lane ends with four channels of one
+// cell and stores them at once.
+//
+// Layer 1 needs, per lane, four pairs of consecutive taps: (x, x + 1) within a
+// kernel row, or the last of a row and the first of the next, 8 or 78 cells
+// on.  The input is staged as arrays of such pairs, and an operand is four
+// LDS reads at constant offsets (not eight of one value and their packing).
 //
 // Layer 2 pairs the kernel rows within one z offset dk (dj = 0 with 1, and
 // dj = 2 alone: 18 MFMAs per 16-cell tile, 27 taps in 32-wide K groups) so
 // that a loaded input slice serves the three output slices it reaches: each
 // wave walks the z-slices of its y-rows and loads every input fragment once
 // (6 per slice), instead of once per output tile (15 per tile).  The
-// x-shifted operands are loaded from A1 one cell to either side; its zero
-// padding supplies the "same" convolution's zeros at the ends of the x-rows
-// (moving one fragment across lanes with DPP row shifts instead costs 16
-// vector instructions per pair for the shifts and row-end masks, which
-// bounded an earlier version).  A1's rows and the layer-3 partial sums are
-// padded so that the 16 lanes of an MFMA column group address different
-// LDS banks.  Activations are rounded to BF16 (nearest even) by the
+// x-shifted operands are loaded from A1 one cell to either side (moving one
+// fragment across lanes with DPP row shifts instead costs 16 vector
+// instructions per pair for the shifts and row-end masks, which bounded an
+// earlier version).  Activations are rounded to BF16 (nearest even) by the
 // hardware conversion.
+//
+// Layer 3 takes the three di of a kernel row into K, so one pass of 9 columns
+// replaces two of 16 and the sum over shifted cells has 9 terms, loaded
+// without branches (with 27 columns it was 54 predicated reads a thread, each
+// waited for by itself).
+//
+// Bound by the latencies between the barriers of a box: three workgroups a CU
+// (168 registers, 45 KB of LDS) keep the matrix cores busy for half of the
+// time.  9473 boxes: 137 us before the pairs, the 9 columns and the row layout
+// below, now 91; LDS instructions 10.5M -> 6.3M, vector instructions 34.9M ->
+// 18.0M.  The LDS matters first: at 54 KB only two workgroups fit, 132 us.
 constexpr int kFwdThreads = 256;  // 4 waves; 3 workgroups per CU
 
 template <bool SAVE>
@@ -136,54 +149,62 @@ __global__ __launch_bounds__(kFwdThreads) __attribute__((amdgpu_waves_per_eu(3, 
                                                         const float *__restrict__ prm,
                                                         uint16_t *__restrict__ a1o,
                                                         uint16_t *__restrict__ a2o) {
-    __shared__ __attribute__((aligned(16))) uint16_t xs[1008];
-    // A1 [1000][16] BF16 (32000 bytes), later one half of Q, [16][kQs] FP32
-    // (rows padded from 512 to kQs floats: the 16 lanes that store one MFMA
-    // result column each write a different row, which then start in
-    // different LDS banks)
-    constexpr int kQs = 516;
-    // A1 layout (u16 units): padded cell (x, y, z) at z*kA1z + y*kA1y + x*16,
-    // each y-row 10 cells + 16 bytes, so that the two x-rows of a 16-cell
-    // tile start in different LDS banks
-    constexpr int kA1y = 168, kA1z = 10 * kA1y, kA1 = 10 * kA1z;
-    constexpr int kR = (16 * kQs > kA1 / 2 ? 16 * kQs : kA1 / 2) / 4;
-    __shared__ __attribute__((aligned(16))) uint4 R[kR];
-    __shared__ __attribute__((aligned(16))) uint16_t A2[512 * 16];
-    uint16_t *A1 = reinterpret_cast<uint16_t *>(R);
-    float *Q = reinterpret_cast<float *>(R);
+    // A1 (u16): cell (x, y, z), y and z padded by one (zero), at (10 z + y) *
+    // kRow + 16 x; A2 the same without padding.  A lane whose x-shifted cell is
+    // outside reads a zero row instead.  Rows of 8 cells, 64 LDS banks, gave
+    // the fewest bank conflicts: 12.4M cycles on 9473 boxes, against 19.0M with
+    // 16 bytes more a row and 24.4M with the halves of the channels apart.
+    constexpr int kRow = 8 * 16, kA1 = 100 * kRow, kA2 = 64 * kRow;
+    // Q [9][kQs] FP32, in A1's space
+    constexpr int kQs = 520, kQ = 9 * kQs;
+    // the pairs of the input, in A2's space: (c, c + 1), (c, c + 8), (c, c + 78)
+    constexpr int kPairs = 1000;
+    static_assert(kQ * 4 <= kA1 * 2 && kQ % 4 == 0 && 3 * kPairs * 4 <= kA2 * 2, "overlays fit");
+    // the weights of layers 1 and 3 and the biases: with the rest in registers
+    // they spilled
+    __shared__ uint4 RA[kA1 / 8], RB[kA2 / 8], W1[64], W3[2][64], Z[1];
+    __shared__ f32x4 bias[8];
+    uint16_t *A1 = reinterpret_cast<uint16_t *>(RA), *A2 = reinterpret_cast<uint16_t *>(RB);
+    float *Q = reinterpret_cast<float *>(RA);
     const int t = threadIdx.x, lane = t & 63, w = t >> 6, row = lane & 15, g = lane >> 4;
     const int o = lane & 15;
+    // the lane's cell of tile (w, z): (i, j, z)
+    const int i = row & 7, j = 2 * w + (row >> 3);
     const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
 
     // ---- weights, once per workgroup
-    const bf16x8 B1 = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(pk + kP1 + lane * 8));
+    if (t < 64) W1[t] = *reinterpret_cast<const uint4 *>(pk + kP1 + t * 8);
+    if (t < 32) reinterpret_cast<float *>(bias)[t] = prm[t < 16 ? kB1 + t : kB2 + t - 16];
     bf16x8 B2[18];
 #pragma unroll
     for (int f = 0; f < 18; f++)
         B2[f] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(pk + kP2 + (f * 64 + lane) * 8));
-    s16x4 B3[2];
+    // layer 3, column o = kernel row 3 dk + dj: di = 0 in K groups 0-1 and
+    // di = 1 in 2-3, then di = 2 and nothing
+    if (t < 128) {
+        u32x4 f = {0u, 0u, 0u, 0u};
+        const int di = t < 64 ? g >> 1 : 2;
+        if (o < 9 && (t < 64 || g < 2)) {
+            const float *p = prm + kW3 + 8 * (g & 1) * 27 + 3 * o + di;
 #pragma unroll
-    for (int nt = 0; nt < 2; nt++) B3[nt] = *reinterpret_cast<const s16x4 *>(pk + kP3 + (nt * 64 + lane) * 4);
-    const float bias1 = prm[kB1 + o], bias2 = prm[kB2 + o], b3 = prm[kB3];
-    int off1[8];  // layer-1 taps of this lane's K group (-1: padding tap 27-31)
-#pragma unroll
-    for (int qq = 0; qq < 8; qq++) {
-        int tp = 8 * g + qq;
-        off1[qq] = tp < 27 ? tap_off(tp) : -1;
-    }
-    // layer 3: which of the 27 taps of this thread's two output cells lie
-    // inside the box (the same for every box)
-    uint32_t inside[2];
-#pragma unroll
-    for (int h = 0; h < 2; h++) {
-        const int c = t + 256 * h, ci = c & 7, cj = (c >> 3) & 7, ck = c >> 6;
-        uint32_t msk = 0;
-        for (int tp = 0; tp < 27; tp++) {
-            int ii = ci + tp % 3 - 1, jj = cj + (tp / 3) % 3 - 1, kk = ck + tp / 9 - 1;
-            if ((unsigned)ii < 8u && (unsigned)jj < 8u && (unsigned)kk < 8u) msk |= 1u << tp;
+            for (int q = 0; q < 4; q++) f[q] = f2bf(p[54 * q]) | ((uint32_t)f2bf(p[54 * q + 27]) << 16);
         }
-        inside[h] = msk;
+        W3[t >> 6][lane] = __builtin_bit_cast(uint4, f);
     }
+    if (t == 0) Z[0] = make_uint4(0, 0, 0, 0);
+    const float b3 = prm[kB3];
+    // layer 1: where the pairs of taps (8 g + 2 h, + 1) of the lane's cell at
+    // z = 0 are; taps 27 to 31 are padding
+    const uint32_t *pair[4];
+#pragma unroll
+    for (int h = 0; h < 4; h++) {
+        const int tp = 8 * g + 2 * h, next = tp / 3 % 3 == 2 ? 2 : 1;
+        const int at = tp < 27 ? tap_off(tp) : 0;
+        pair[h] = reinterpret_cast<const uint32_t *>(RB) + (tp < 27 && tp % 3 == 2 ? next * kPairs : 0) + at + j * 10 + i;
+    }
+    const uint32_t last = g == 3 ? 0x0000ffffu : 0xffffffffu, none = g == 3 ? 0u : 0xffffffffu;
+    const int put = i * 16 + 4 * g;  // where the lane's four channels of a cell go
+    const uint32_t save = 4 * g * 512 + j * 8 + i;
     int64_t q = blockIdx.x;
     float xn[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     if (q < nbox) {
@@ -192,13 +213,24 @@ __global__ __launch_bounds__(kFwdThreads) __attribute__((amdgpu_waves_per_eu(3, 
         for (int h = 0; h < 4; h++)
             if (t + 256 * h < 1000) xn[h] = xb[t + 256 * h];
     }
+    // A1's padding is zero; a box overwrites the part that holds Q
+    for (int e = t + kQ / 4; e < kA1 / 8; e += kFwdThreads) RA[e] = make_uint4(0, 0, 0, 0);
     for (; q < nbox; q += gridDim.x) {
         __syncthreads();  // the previous box is done with every LDS buffer
-        // zero A1 (its padding must be 0; Q of the previous box overwrote it)
-        for (int e = t; e < kA1 / 8; e += kFwdThreads) R[e] = make_uint4(0, 0, 0, 0);
+        for (int e = t; e < kQ / 4; e += kFwdThreads) RA[e] = make_uint4(0, 0, 0, 0);
 #pragma unroll
-        for (int h = 0; h < 4; h++)
-            if (t + 256 * h < 1000) xs[t + 256 * h] = f2bf_hw(xn[h]);
+        for (int h = 0; h < 4; h++) {
+            const int c = t + 256 * h;
+            const uint16_t v = f2bf_hw(xn[h]);
+            if (c < 1000) {
+                A2[2 * c] = v;
+                A2[2 * (kPairs + c)] = v;
+                A2[2 * (2 * kPairs + c)] = v;
+                if (h > 0 || c >= 1) *(volatile uint16_t *)(A2 + 2 * c - 1) = v;  // (not one misaligned store with A2[2 c])
+                if (h > 0 || c >= 8) A2[2 * (kPairs + c - 8) + 1] = v;
+                if (h > 0 || c >= 78) A2[2 * (2 * kPairs + c - 78) + 1] = v;
+            }
+        }
         const int64_t qn = q + gridDim.x;
         if (qn < nbox) {
             const float *xb = x + (idx ? (int64_t)idx[qn] : qn) * 1000;
@@ -208,118 +240,110 @@ __global__ __launch_bounds__(kFwdThreads) __attribute__((amdgpu_waves_per_eu(3, 
         }
         __syncthreads();
         // ---- layer 1: K = 27 taps (padded to 32) of the input
-#pragma unroll 1
-        for (int mm = 0; mm < 8; mm++) {
-            const int m = w + 4 * mm;
-            int cell = 16 * m + row, i = cell & 7, j = (cell >> 3) & 7, k = cell >> 6;
-            int base = (k * 10 + j) * 10 + i;
-            uint32_t wv[4];
+        const bf16x8 B1 = __builtin_bit_cast(bf16x8, W1[lane]);
+        const f32x4 bias1 = bias[g];
+#pragma unroll 4
+        for (int k = 0; k < 8; k++) {
+            u32x4 f;
 #pragma unroll
-            for (int h = 0; h < 4; h++) {
-                uint32_t lo = off1[2 * h] >= 0 ? xs[base + off1[2 * h]] : 0u;
-                uint32_t hi = off1[2 * h + 1] >= 0 ? xs[base + off1[2 * h + 1]] : 0u;
-                wv[h] = lo | (hi << 16);
-            }
-            bf16x8 A = __builtin_bit_cast(bf16x8, make_uint4(wv[0], wv[1], wv[2], wv[3]));
-            f32x4 D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, B1, zero, 0, 0, 0);
+            for (int h = 0; h < 4; h++) f[h] = pair[h][100 * k];
+            f[1] &= last;
+            f[2] &= none;
+            f[3] &= none;
+            const f32x4 D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(B1, __builtin_bit_cast(bf16x8, f), zero, 0, 0, 0);
             u16x4 av;
 #pragma unroll
-            for (int r = 0; r < 4; r++) {
-                int c = 16 * m + 4 * g + r, pi = c & 7, pj = (c >> 3) & 7, pk3 = c >> 6;
-                av[r] = f2bf_hw(relu(D[r] + bias1));
-                A1[(pk3 + 1) * kA1z + (pj + 1) * kA1y + (pi + 1) * 16 + o] = av[r];
+            for (int r = 0; r < 4; r++) av[r] = f2bf_hw(relu(D[r] + bias1[r]));
+            *reinterpret_cast<u16x4 *>(A1 + (10 * (k + 1) + j + 1) * kRow + put) = av;
+            if (SAVE) {  // a1 for training, [box][channel][cell]
+#pragma unroll
+                for (int r = 0; r < 4; r++) (a1o + q * 8192)[save + r * 512 + k * 64] = av[r];
             }
-            // a1 for training, [box][channel][cell]: the lane's four cells
-            if (SAVE) *reinterpret_cast<u16x4 *>(a1o + q * 8192 + (o * 512 + 4 * g + 16 * m)) = av;
         }
         __syncthreads();
-        // ---- layer 2, blocked along z: wave w owns the output tiles of
-        // y-rows (2w, 2w+1) at every z.  Each padded input slice zs is loaded
+        // ---- layer 2, blocked along z.  Each padded input slice zs is loaded
         // once (per x-shift di: the kernel rows dj = 0 | 1 in K groups 0-1 |
         // 2-3, and dj = 2 | nothing) and feeds the three output slices
         // k = zs - dk it reaches; an output slice is complete after its
-        // input slice k + 2.  The x-shifted operands come from the
-        // zero-padded A1 one cell to either side.
+        // input slice k + 2.  Cells outside and "nothing" are read from the
+        // zero y-row 0.
         {
-            const int i = row & 7, jj = 2 * w + (row >> 3);
-            const int colA = (g < 2 ? 0 : 1) * kA1y, colB = 2 * kA1y;  // kernel row dj of each K group
+            const uint16_t *srcA[3], *srcB[3];
+#pragma unroll
+            for (int di = 0; di < 3; di++) {
+                const int at = ((i + di - 1) & 7) * 16 + 8 * (g & 1);
+                const bool in = (unsigned)(i + di - 1) < 8u;
+                srcA[di] = A1 + (in ? (j + (g >> 1)) * kRow : 0) + at;
+                srcB[di] = A1 + (in && g < 2 ? (j + 2) * kRow : 0) + at;
+            }
+            const f32x4 bias2 = bias[4 + g];
             f32x4 acc[3] = {zero, zero, zero};
 #pragma unroll
             for (int zs = 0; zs < 10; zs++) {
-                const uint16_t *src = A1 + zs * kA1z + jj * kA1y + i * 16 + 8 * (g & 1);
-                uint4 FA[3], FB[3];
+                bf16x8 FA[3], FB[3];
 #pragma unroll
                 for (int di = 0; di < 3; di++) {
-                    FA[di] = *reinterpret_cast<const uint4 *>(src + colA + di * 16);
-                    FB[di] = g < 2 ? *reinterpret_cast<const uint4 *>(src + colB + di * 16) : make_uint4(0, 0, 0, 0);
+                    FA[di] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(srcA[di] + 10 * zs * kRow));
+                    FB[di] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(srcB[di] + 10 * zs * kRow));
                 }
 #pragma unroll
-                for (int dk = 0; dk < 3; dk++) {
-                    const int k = zs - dk;
-                    if (k < 0 || k > 7) continue;
+                for (int e = 0; e < 6; e++) {  // in each sum: di, then its two fragments
 #pragma unroll
-                    for (int di = 0; di < 3; di++) {
-                        acc[k % 3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            __builtin_bit_cast(bf16x8, FA[di]), B2[(dk * 2 + 0) * 3 + di], acc[k % 3], 0, 0, 0);
-                        acc[k % 3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            __builtin_bit_cast(bf16x8, FB[di]), B2[(dk * 2 + 1) * 3 + di], acc[k % 3], 0, 0, 0);
+                    for (int dk = 0; dk < 3; dk++) {
+                        const int k = zs - dk, di = e >> 1;
+                        if (k < 0 || k > 7) continue;
+                        acc[k % 3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(B2[(dk * 2 + (e & 1)) * 3 + di],
+                                                                             e & 1 ? FB[di] : FA[di], acc[k % 3], 0, 0, 0);
                     }
                 }
                 const int kd = zs - 2;  // the output slice completed by this input slice
                 if (kd >= 0) {
-                    const int m = 4 * kd + w;
                     u16x4 av;
 #pragma unroll
-                    for (int r = 0; r < 4; r++) {
-                        int c = 16 * m + 4 * g + r;
-                        av[r] = f2bf_hw(relu(acc[kd % 3][r] + bias2));
-                        A2[c * 16 + o] = av[r];
+                    for (int r = 0; r < 4; r++) av[r] = f2bf_hw(relu(acc[kd % 3][r] + bias2[r]));
+                    *reinterpret_cast<u16x4 *>(A2 + (kd * 8 + j) * kRow + put) = av;
+                    if (SAVE) {
+#pragma unroll
+                        for (int r = 0; r < 4; r++) (a2o + q * 8192)[save + r * 512 + kd * 64] = av[r];
                     }
-                    if (SAVE) *reinterpret_cast<u16x4 *>(a2o + q * 8192 + (o * 512 + 4 * g + 16 * m)) = av;
                     acc[kd % 3] = zero;
                 }
             }
         }
         __syncthreads();  // A1 is dead; its space holds Q from here on
-        // ---- layer 3: Q[tap][cell] = sum_c W3[c][tap] a2[c][cell], taps
-        // 0-15 now and 16-26 after the first half of the sum
-#pragma unroll 2
-        for (int mm = 0; mm < 8; mm++) {
-            const int m = w + 4 * mm;
-            int cell = 16 * m + row;
-            s16x4 A = *reinterpret_cast<const s16x4 *>(A2 + cell * 16 + 4 * g);
-            f32x4 D = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(A, B3[0], zero, 0, 0, 0);
-            *reinterpret_cast<f32x4 *>(Q + o * kQs + 16 * m + 4 * g) = D;
+        // ---- layer 3: Q[kernel row][cell], from the cells (x - 1 | x) and
+        // (x + 1 | nothing) in K groups 0-1 | 2-3
+        const bf16x8 B3a = __builtin_bit_cast(bf16x8, W3[0][lane]), B3b = __builtin_bit_cast(bf16x8, W3[1][lane]);
+        const int xa = i + (g >> 1) - 1;
+        const uint16_t *none3 = reinterpret_cast<const uint16_t *>(Z), *src3 = A2 + j * kRow + 8 * (g & 1);
+#pragma unroll 4
+        for (int k = 0; k < 8; k++) {
+            const uint16_t *pa = xa >= 0 ? src3 + k * 8 * kRow + xa * 16 : none3;
+            const uint16_t *pb = g < 2 && i < 7 ? src3 + k * 8 * kRow + (i + 1) * 16 : none3;
+            const bf16x8 Fa = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(pa));
+            const bf16x8 Fb = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(pb));
+            f32x4 D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Fa, B3a, zero, 0, 0, 0);
+            D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Fb, B3b, D, 0, 0, 0);
+            if (o < 9) *reinterpret_cast<f32x4 *>(Q + o * kQs + 16 * (w + 4 * k) + 4 * g) = D;
         }
         __syncthreads();
-        float s[2];
+        // kernel rows outside the box read a zero
+        const int oj = (t >> 2) & 7, ok = t >> 5;
+        float2 s[9];
 #pragma unroll
-        for (int h = 0; h < 2; h++) {
-            const int c = t + 256 * h;
-            s[h] = b3;
-#pragma unroll
-            for (int tp = 0; tp < 16; tp++)
-                if ((inside[h] >> tp) & 1u) s[h] += Q[tp * kQs + c + (tp / 9 - 1) * 64 + ((tp / 3) % 3 - 1) * 8 + tp % 3 - 1];
+        for (int e = 0; e < 9; e++) {
+            const int dk = e / 3 - 1, dj = e % 3 - 1;
+            const bool in = (dk < 0 ? ok > 0 : dk > 0 ? ok < 7 : true) && (dj < 0 ? oj > 0 : dj > 0 ? oj < 7 : true);
+            const float *p = in ? Q + e * kQs + 2 * t + dk * 64 + dj * 8 : reinterpret_cast<const float *>(Z);
+            s[e] = *reinterpret_cast<const float2 *>(p);
         }
-        __syncthreads();
-#pragma unroll 2
-        for (int mm = 0; mm < 8; mm++) {
-            const int m = w + 4 * mm;
-            int cell = 16 * m + row;
-            s16x4 A = *reinterpret_cast<const s16x4 *>(A2 + cell * 16 + 4 * g);
-            f32x4 D = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(A, B3[1], zero, 0, 0, 0);
-            if (o < 11) *reinterpret_cast<f32x4 *>(Q + o * kQs + 16 * m + 4 * g) = D;
-        }
-        __syncthreads();
+        float2 sum = make_float2(b3, b3);
 #pragma unroll
-        for (int h = 0; h < 2; h++) {
-            const int c = t + 256 * h;
-#pragma unroll
-            for (int tp = 16; tp < 27; tp++)
-                if ((inside[h] >> tp) & 1u)
-                    s[h] += Q[(tp - 16) * kQs + c + (tp / 9 - 1) * 64 + ((tp / 3) % 3 - 1) * 8 + tp % 3 - 1];
-            y[q * 512 + c] = s[h];
+        for (int e = 0; e < 9; e++) {
+            sum.x += s[e].x;
+            sum.y += s[e].y;
         }
+        *reinterpret_cast<float2 *>(y + q * 512 + 2 * t) = sum;
     }
 }
 

@@ -87,6 +87,23 @@ def test_forward_special_cases():
     assert np.array_equal(net.get_params(), p)
 
 
+@pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("at", [(0, 0, 0), (9, 9, 9), (4, 0, 9), (5, 4, 3)])
+def test_forward_non_finite_input_stays_local(bad, at):
+    """A non-finite input cell reaches the outputs whose kernels cover it and
+    no other: the padding taps and the zero operands of a tile take no part."""
+    p = rand_params(3)
+    x = rand_x(5, 3)
+    x[1][at] = bad
+    y = NN.Net(p).forward(torch.from_numpy(x).cuda()).cpu().numpy().astype(np.float64)
+    with np.errstate(all="ignore"):
+        ref, _ = N.forward(p.astype(np.float64), x.astype(np.float64))
+    ok = np.isfinite(ref)
+    assert (~ok).any() and ok[0].all() and ok[2].all()
+    assert np.array_equal(np.isfinite(y), ok)
+    assert np.abs(y - ref)[ok].max() <= FWD_MAX * np.abs(ref[ok]).max()
+
+
 def segments():
     return [("W1", 0, N.N_W1), ("b1", N.N_W1, 16), ("W2", N.N_W1 + 16, N.N_W2),
             ("b2", N.N_W1 + 16 + N.N_W2, 16), ("W3", N.N_W1 + 32 + N.N_W2, N.N_W3),
