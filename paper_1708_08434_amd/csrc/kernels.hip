@@ -815,6 +815,168 @@ __global__ __launch_bounds__(256) void k_cf_coarse(Geo g, const T *__restrict__ 
     cf_face<T>(g, phi, chat, slots, s0 + s, threadIdx.x & 63);
 }
 
+// A whole box for a 7-point stencil on all of its cells, 128 threads: thread u
+// holds the four cells i = 4 h .. 4 h + 3 (h = u & 1) of row j = (u >> 1) & 7,
+// k = u >> 4, which are the colour positions 2u and 2u + 1 of both colours.
+// The box and its y and z ghosts lie in a grid G[10][10][8] and the x ghosts in
+// X[2][64], so that the rows on all sides are read in pairs at constant
+// offsets; the ghosts of axis a are the a-th value of a thread (wave 0 the low
+// side), so that the axis is a compile-time constant, and all loads go out
+// before the first wait.  (With a colour-split copy and a table of ghosts, each
+// of the 24 neighbour reads a thread picked its address; the stencil kernels
+// then issued 900 to 1135 instructions a wavefront, now 500 to 690; on 206000
+// boxes the stopping test went from 445 to 395 us.)
+constexpr int kFullG = 800, kFullX = 128;
+template <int A> __device__ __forceinline__ int full_off(int layer, int u, int v) {
+    return ((layer + u + v) & 1) * 256 +
+           (A == 0 ? (v * 8 + u) * 4 + (layer >> 1) : A == 1 ? (v * 8 + layer) * 4 + (u >> 1) : (layer * 8 + v) * 4 + (u >> 1));
+}
+template <int A> __device__ __forceinline__ int full_place(int layer, int u, int v) {
+    return A == 0 ? (v * 10 + u + 11) * 8 + layer : A == 1 ? ((v + 1) * 10 + layer + 1) * 8 + u : ((layer + 1) * 10 + v + 1) * 8 + u;
+}
+// The four cells of a thread from its two values of each colour, and back; odd
+// = (j + k) & 1.
+template <typename T, typename V>
+__device__ __forceinline__ void to_cells(V c0, V c1, bool odd, T v[4]) {
+    v[0] = odd ? c1.x : c0.x;
+    v[1] = odd ? c0.x : c1.x;
+    v[2] = odd ? c1.y : c0.y;
+    v[3] = odd ? c0.y : c1.y;
+}
+// Stage box b (ZERO: of the zero field, which is not read) and leave the
+// thread's cells in own.  Ends with a barrier.
+template <typename T, bool ZERO>
+__device__ __forceinline__ void full_stage(const Geo &g, const T *__restrict__ phi, const T *__restrict__ chat,
+                                           int64_t b, T *G, T *X, T own[4]) {
+    using V = typename VecN<T, 2>::type;
+    const int u = threadIdx.x, side = __builtin_amdgcn_readfirstlane(u >> 6), fu = u & 7, fv = (u >> 3) & 7;
+    const int edge = side ? 7 : 0, in = side ? 6 : 1;
+    const FaceTab ft = face_tab(g, b);
+    V p0, p1;
+    p0.x = p0.y = p1.x = p1.y = (T)0;
+    if (!ZERO) {
+        p0 = reinterpret_cast<const V *>(phi + b * 512)[u];
+        p1 = reinterpret_cast<const V *>(phi + b * 512 + 256)[u];
+    }
+    bool bnd = false;
+#pragma unroll
+    for (int d = 0; d < 6; d++) bnd = bnd || ft.nb[d] < 0;
+    T raw[3];
+    int nb[3];
+    auto load = [&](auto A) __attribute__((always_inline)) {
+        constexpr int a = decltype(A)::a;
+        const int d = 2 * a + side, slot = side ? ft.slot[2 * a + 1] : ft.slot[2 * a];
+        nb[a] = side ? ft.nb[2 * a + 1] : ft.nb[2 * a];
+        raw[a] = (T)0;
+        if (nb[a] >= 0) {
+            if (!ZERO) raw[a] = (phi + (int64_t)nb[a] * 512)[full_off<a>(7 - edge, fu, fv)];
+        } else if (nb[a] == -1) {
+            raw[a] = (chat + (int64_t)slot * 64)[fv * 8 + fu];
+        } else if (g.bcval) {
+            raw[a] = (T)(g.bcval + (b * 6 + d) * 64)[fv * 8 + fu];
+        }
+    };
+    load(Axis<0>());
+    load(Axis<1>());
+    load(Axis<2>());
+    const int h = u & 1, j = (u >> 1) & 7, k = u >> 4, at = (k * 10 + j + 11) * 8 + 4 * h;
+    to_cells<T, V>(p0, p1, (j + k) & 1, own);
+    V w;
+    w.x = own[0];
+    w.y = own[1];
+    *reinterpret_cast<V *>(G + at) = w;
+    w.x = own[2];
+    w.y = own[3];
+    *reinterpret_cast<V *>(G + at + 2) = w;
+    auto put = [&](auto A, T v) __attribute__((always_inline)) {
+        constexpr int a = decltype(A)::a;
+        if (a == 0)
+            X[side * 64 + fv * 8 + fu] = v;
+        else
+            G[full_place<a>(side ? 8 : -1, fu, fv)] = v;
+    };
+    put(Axis<0>(), raw[0]);
+    put(Axis<1>(), raw[1]);
+    put(Axis<2>(), raw[2]);
+    __syncthreads();
+    if (bnd) {  // block-uniform: boundary ghosts read the box's cells
+        auto ghost = [&](auto A) __attribute__((always_inline)) {
+            constexpr int a = decltype(A)::a;
+            if (nb[a] >= 0) return;
+            const int d = 2 * a + side;
+            T v = G[full_place<a>(edge, fu, fv)];
+            if (nb[a] == -1)
+                v = cf_ghost<T>(raw[a], v, G[full_place<a>(in, fu, fv)]);
+            else if (g.bct[d] != 1)
+                v = dirichlet_ghost<T>(g.bcval ? raw[a] : (T)g.bcv[d], v);
+            put(A, v);
+        };
+        ghost(Axis<0>());
+        ghost(Axis<1>());
+        ghost(Axis<2>());
+        __syncthreads();
+    }
+}
+// The neighbour sums of the thread's four cells, in sum_full's order.
+template <typename T> __device__ __forceinline__ void full_sums(const T *G, const T *X, const T own[4], T s[4]) {
+    using V = typename VecN<T, 2>::type;
+    const int u = threadIdx.x, h = u & 1, row = u >> 1, at = ((u >> 4) * 10 + (row & 7) + 11) * 8 + 4 * h;
+    const T lo = *(h ? G + at - 1 : X + row), hi = *(h ? X + 64 + row : G + at + 4);
+    s[0] = lo + own[1];
+    s[1] = own[0] + own[2];
+    s[2] = own[1] + own[3];
+    s[3] = own[2] + hi;
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        const T *p = G + at + (q == 0 ? -8 : q == 1 ? 8 : q == 2 ? -80 : 80);
+        const V a = *reinterpret_cast<const V *>(p), c = *reinterpret_cast<const V *>(p + 2);
+        s[0] += a.x;
+        s[1] += a.y;
+        s[2] += c.x;
+        s[3] += c.y;
+    }
+}
+// Stages 16 .. 1 of a sum over 32 lanes (each half of a wavefront), every lane
+// getting x[i] + x[i ^ w] in that order.  Below 16 the partner of a lane within
+// its row of 16 is also w lanes on (the values repeat with period 2 w), which
+// a row rotation reaches without LDS.
+template <int W> __device__ __forceinline__ double row_ror(double x) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, 0x120 + W, 0xf, 0xf, true);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x120 + W, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ double half_sum(double x) {
+    x += __shfl_xor(x, 16);
+    x += row_ror<8>(x);
+    x += row_ror<4>(x);
+    x += row_ror<2>(x);
+    x += row_ror<1>(x);
+    return x;
+}
+__device__ __forceinline__ double half_max(double x) {
+    x = nanmax(__shfl_xor(x, 16), x);
+    x = nanmax(row_ror<8>(x), x);
+    x = nanmax(row_ror<4>(x), x);
+    x = nanmax(row_ror<2>(x), x);
+    x = nanmax(row_ror<1>(x), x);
+    return x;
+}
+// Norms of a box from its thread's residuals: the sums follow k_leaf_norms' tree
+// over the 256 positions (stages 32..2 over the threads, stage 1 the pair), so
+// the partials are the same bits.
+__device__ __forceinline__ void full_norms(const double r[4], bool odd, double *S, double *M) {
+    const int u = threadIdx.x;
+    // position 2u is cells 0 and 1, position 2u + 1 cells 2 and 3, red first
+    const double s0 = half_sum(fmadd(odd ? r[0] : r[1], odd ? r[0] : r[1], (odd ? r[1] : r[0]) * (odd ? r[1] : r[0])));
+    const double s1 = half_sum(fmadd(odd ? r[2] : r[3], odd ? r[2] : r[3], (odd ? r[3] : r[2]) * (odd ? r[3] : r[2])));
+    const double m = half_max(nanmax(nanmax(fabs(r[0]), fabs(r[1])), nanmax(fabs(r[2]), fabs(r[3]))));
+    if ((u & 31) == 0) {
+        S[u >> 5] = s0 + s1;
+        M[u >> 5] = m;
+    }
+}
+
 // Residual on level l and restriction to level l-1 (full approximation
 // scheme): the residual of all 512 cells goes to LDS, then each of 64 threads
 // owns one parent cell and writes phi_c = mean(phi), old_c = phi_c and
@@ -847,10 +1009,8 @@ __global__ __launch_bounds__(128) void k_resid_restrict(Geo g, T *__restrict__ p
                                                         int64_t nleaf_prev, T inv_h2,
                                                         const int32_t *__restrict__ leafpos,
                                                         double *__restrict__ partial, double vol) {
-    // 128 threads per box: thread u holds cell positions 2u and 2u+1 of both
-    // colours (paired loads); the ZERO norm partials follow k_box_norms' tree
     using V = typename VecN<T, 2>::type;
-    __shared__ T P[512], H[384], R[512];
+    __shared__ __attribute__((aligned(16))) T G[kFullG], X[kFullX], R[512];
     __shared__ double S[4], M[4];
     int64_t blk = blockIdx.x;
     const int u = threadIdx.x;
@@ -876,60 +1036,23 @@ __global__ __launch_bounds__(128) void k_resid_restrict(Geo g, T *__restrict__ p
     const int bi = g.ijk[b * 4] & 1, bj = g.ijk[b * 4 + 1] & 1, bk = g.ijk[b * 4 + 2] & 1;
     const V r0 = ld_stream(reinterpret_cast<const V *>(rhs + b * 512) + u);
     const V r1 = ld_stream(reinterpret_cast<const V *>(rhs + b * 512 + 256) + u);
-    const FaceTab ft = face_tab(g, b);
-    if (ZERO) {
-        V z;
-        z.x = (T)0;
-        z.y = (T)0;
-        reinterpret_cast<V *>(P)[u] = z;
-        reinterpret_cast<V *>(P)[128 + u] = z;
+    T own[4], sm[4], f[4];
+    full_stage<T, ZERO>(g, phi, chat, b, G, X, own);
+    const bool odd = ((u >> 1) + (u >> 4)) & 1;
+    to_cells<T, V>(r0, r1, odd, f);
+    full_sums<T>(G, X, own, sm);
 #pragma unroll
-        for (int r = 0; r < 3; r++) {
-            int e = u + 128 * r, d = e >> 6, w = e & 63;
-            H[e] = ghost_of_zero<T>(g, chat, b, d, pick6(ft.nb, d), pick6(ft.slot, d), w & 7, w >> 3);
-        }
-    } else {
-        const V p0 = reinterpret_cast<const V *>(phi + b * 512)[u];
-        const V p1 = reinterpret_cast<const V *>(phi + b * 512 + 256)[u];
+    for (int q = 0; q < 4; q++) sm[q] = resid_of<T>(f[q], sm[q], own[q], inv_h2);
 #pragma unroll
-        for (int r = 0; r < 3; r++) {
-            int e = u + 128 * r, d = e >> 6, w = e & 63;
-            H[e] = ghost_at<T>(g, phi, chat, b, d, pick6(ft.nb, d), pick6(ft.slot, d), w & 7, w >> 3);
-        }
-        reinterpret_cast<V *>(P)[u] = p0;
-        reinterpret_cast<V *>(P)[128 + u] = p1;
-    }
-    __syncthreads();
-    double ss[2] = {0.0, 0.0}, mx[2] = {0.0, 0.0};
-#pragma unroll
-    for (int sl = 0; sl < 2; sl++) {
-        const int t = 2 * u + sl;
-        const int m = t & 3, j = (t >> 2) & 7, k = t >> 5;
-#pragma unroll
-        for (int c = 0; c < 2; c++) {
-            int i = 2 * m + ((j + k + c) & 1);
-            T rc = c ? (sl ? r1.y : r1.x) : (sl ? r0.y : r0.x);
-            T r = resid_of<T>(rc, sum_full<T>(P, H, i, j, k), P[c * 256 + t], inv_h2);
-            R[c * 256 + t] = r;
-            if (ZERO) {
-                ss[sl] = fmadd((double)r, (double)r, ss[sl]);
-                mx[sl] = nanmax(fabs((double)r), mx[sl]);
-            }
-        }
+    for (int q = 0; q < 2; q++) {
+        V w;
+        w.x = sm[2 * q];
+        w.y = sm[2 * q + 1];
+        *reinterpret_cast<V *>(R + 4 * u + 2 * q) = w;  // natural order
     }
     if (ZERO && leafpos[b] >= 0) {  // block-uniform
-#pragma unroll
-        for (int off = 16; off > 0; off >>= 1) {
-#pragma unroll
-            for (int sl = 0; sl < 2; sl++) {
-                ss[sl] += __shfl_xor(ss[sl], off);
-                mx[sl] = nanmax(__shfl_xor(mx[sl], off), mx[sl]);
-            }
-        }
-        if ((u & 31) == 0) {
-            S[u >> 5] = ss[0] + ss[1];
-            M[u >> 5] = nanmax(mx[1], mx[0]);
-        }
+        const double r[4] = {(double)sm[0], (double)sm[1], (double)sm[2], (double)sm[3]};
+        full_norms(r, odd, S, M);
     }
     __syncthreads();
     if (ZERO && u == 0 && leafpos[b] >= 0) {
@@ -937,25 +1060,27 @@ __global__ __launch_bounds__(128) void k_resid_restrict(Geo g, T *__restrict__ p
         partial[2 * q] = ((S[0] + S[1]) + (S[2] + S[3])) * vol;
         partial[2 * q + 1] = nanmax(nanmax(M[0], M[1]), nanmax(M[2], M[3]));
     }
-    if (u < 64) {
-        int pi = u & 3, pj = (u >> 2) & 3, pk = u >> 4;
-        T sphi = 0, sres = 0;
+    // a parent cell a thread: wave 0 the mean of phi, wave 1 of the residual
+    const int pi = u & 3, pj = (u >> 2) & 3, pk = (u >> 4) & 3;
+    const bool res = __builtin_amdgcn_readfirstlane(u >> 6);
+    const T *src = res ? R + (pk * 16 + pj * 2) * 8 + 2 * pi : G + (pk * 20 + pj * 2 + 11) * 8 + 2 * pi;
+    const int zs = res ? 64 : 80;
+    T mean = 0;
 #pragma unroll
-        for (int dk = 0; dk < 2; dk++)
+    for (int dk = 0; dk < 2; dk++)
 #pragma unroll
-            for (int dj = 0; dj < 2; dj++)
-#pragma unroll
-                for (int di = 0; di < 2; di++) {
-                    int c = cs_idx(2 * pi + di, 2 * pj + dj, 2 * pk + dk);
-                    sphi += P[c];
-                    sres += R[c];
-                }
-        int ci = 4 * bi + pi, cj = 4 * bj + pj, ck = 4 * bk + pk;
-        int64_t pc = p * 512 + cs_idx(ci, cj, ck);
-        T mphi = (T)0.125 * sphi;
-        phi[pc] = mphi;
-        old[pc] = mphi;
-        rhs[pc] = (T)0.125 * sres;
+        for (int dj = 0; dj < 2; dj++) {
+            const V w = *reinterpret_cast<const V *>(src + dk * zs + dj * 8);
+            mean += w.x;
+            mean += w.y;
+        }
+    mean = (T)0.125 * mean;
+    const int64_t pc = p * 512 + cs_idx(4 * bi + pi, 4 * bj + pj, 4 * bk + pk);
+    if (res) {
+        rhs[pc] = mean;
+    } else {
+        phi[pc] = mean;
+        old[pc] = mean;
     }
 }
 
@@ -966,43 +1091,28 @@ __global__ __launch_bounds__(128) void k_fas_rhs(Geo g, const T *__restrict__ ph
                                                  const T *__restrict__ chat,
                                                  const int32_t *__restrict__ list, int64_t nlist,
                                                  T inv_h2) {
-    // 128 threads per box: thread u holds cell positions 2u and 2u+1 of both
-    // colours (paired loads and stores)
     using V = typename VecN<T, 2>::type;
-    __shared__ T P[512], H[384];
+    __shared__ __attribute__((aligned(16))) T G[kFullG], X[kFullX];
     int64_t q = xcd_map(blockIdx.x, nlist);
     if (q >= nlist) return;
     int64_t b = list[q];
     const int u = threadIdx.x;
     const V r0 = ld_stream(reinterpret_cast<const V *>(rhs + b * 512) + u);
     const V r1 = ld_stream(reinterpret_cast<const V *>(rhs + b * 512 + 256) + u);
-    const V p0 = reinterpret_cast<const V *>(phi + b * 512)[u];
-    const V p1 = reinterpret_cast<const V *>(phi + b * 512 + 256)[u];
-    const FaceTab ft = face_tab(g, b);
+    T own[4], s[4], f[4];
+    full_stage<T, false>(g, phi, chat, b, G, X, own);
+    const bool odd = ((u >> 1) + (u >> 4)) & 1;
+    to_cells<T, V>(r0, r1, odd, f);
+    full_sums<T>(G, X, own, s);
 #pragma unroll
-    for (int r = 0; r < 3; r++) {
-        int e = u + 128 * r, d = e >> 6, w = e & 63;
-        H[e] = ghost_at<T>(g, phi, chat, b, d, pick6(ft.nb, d), pick6(ft.slot, d), w & 7, w >> 3);
-    }
-    reinterpret_cast<V *>(P)[u] = p0;
-    reinterpret_cast<V *>(P)[128 + u] = p1;
-    __syncthreads();
-    const T *rr0 = reinterpret_cast<const T *>(&r0), *rr1 = reinterpret_cast<const T *>(&r1);
-#pragma unroll
-    for (int c = 0; c < 2; c++) {
-        V out;
-        T *o = reinterpret_cast<T *>(&out);
-#pragma unroll
-        for (int sl = 0; sl < 2; sl++) {
-            const int t = 2 * u + sl;
-            const int m = t & 3, j = (t >> 2) & 7, k = t >> 5;
-            int i = 2 * m + ((j + k + c) & 1);
-            T own = P[c * 256 + t];
-            T s = sum_full<T>(P, H, i, j, k);
-            o[sl] = (s - (T)6 * own) * inv_h2 + (c ? rr1[sl] : rr0[sl]);
-        }
-        reinterpret_cast<V *>(rhs + b * 512 + c * 256)[u] = out;
-    }
+    for (int e = 0; e < 4; e++) s[e] = (s[e] - (T)6 * own[e]) * inv_h2 + f[e];
+    V w;
+    w.x = odd ? s[1] : s[0];
+    w.y = odd ? s[3] : s[2];
+    reinterpret_cast<V *>(rhs + b * 512)[u] = w;
+    w.x = odd ? s[0] : s[1];
+    w.y = odd ? s[2] : s[3];
+    reinterpret_cast<V *>(rhs + b * 512 + 256)[u] = w;
 }
 
 // phi_f += 1/4 delta(C) + 1/4 (delta(C + s_x) + delta(C + s_y) + delta(C + s_z))
@@ -1872,11 +1982,7 @@ __global__ __launch_bounds__(256) void k_leaf_norms(Geo g, const double *__restr
 // the leaf list (XCD-aware mapping of q): over the box range instead, the
 // refined boxes, which exit at once, crowd the first shares (on the
 // two-streamer tree the busiest XCD had 14% more leaf boxes than the mean).
-// 128 threads per box with paired loads keep twice the boxes in flight.
-// Thread u holds cell positions 2u and 2u+1 of both colours; the per-box sum
-// follows k_leaf_norms' tree over the 256 positions (the shuffles over u
-// are its stages 32..2, the pair sum its stage 1), so the partials are the
-// same bits.  With h = len 2^-(l+2), 1/h^2 and h^3 are the power-of-two
+// With h = len 2^-(l+2), 1/h^2 and h^3 are the power-of-two
 // scalings ilen2 2^(2(l+2)) and len3 2^(-3(l+2)) of ilen2 = 1/len^2 and
 // len3 = len^3 (the same bits as dividing, in the normal range), so the
 // kernel holds no divide.  OUT: the FP32 residual is also stored.
@@ -1887,61 +1993,29 @@ __global__ __launch_bounds__(128) void k_box_norms(Geo g, const double *__restri
                                                    const int32_t *__restrict__ leaf, int64_t q0, int64_t nq,
                                                    double *__restrict__ partial, float *__restrict__ r_out,
                                                    double ilen2, double len3) {
-    __shared__ double P[512], H[384], S[4], M[4];
+    __shared__ __attribute__((aligned(16))) double G[kFullG], X[kFullX];
+    __shared__ double S[4], M[4];
     int64_t lq = xcd_map(blockIdx.x, nq);
     if (lq >= nq) return;
     const int64_t q = q0 + lq;
     const int64_t b = leaf[q];
     const int u = threadIdx.x;
-    const double2 p0 = reinterpret_cast<const double2 *>(phi + b * 512)[u];
-    const double2 p1 = reinterpret_cast<const double2 *>(phi + b * 512 + 256)[u];
     const double2 r0 = ld_stream(reinterpret_cast<const double2 *>(rhs + b * 512) + u);
     const double2 r1 = ld_stream(reinterpret_cast<const double2 *>(rhs + b * 512 + 256) + u);
-    const FaceTab ft = face_tab(g, b);
-#pragma unroll
-    for (int r = 0; r < 3; r++) {
-        int e = u + 128 * r, d = e >> 6, w = e & 63;
-        H[e] = ghost_at<double>(g, phi, chat, b, d, pick6(ft.nb, d), pick6(ft.slot, d), w & 7, w >> 3);
-    }
-    reinterpret_cast<double2 *>(P)[u] = p0;
-    reinterpret_cast<double2 *>(P)[128 + u] = p1;
-    __syncthreads();
     const int l = g.ijk[b * 4 + 3];
+    double own[4], r[4], f[4];
+    full_stage<double, false>(g, phi, chat, b, G, X, own);
+    const bool odd = ((u >> 1) + (u >> 4)) & 1;
+    to_cells<double, double2>(r0, r1, odd, f);
+    full_sums<double>(G, X, own, r);
     const double inv_h2 = ldexp(ilen2, 2 * (l + 2)), vol = ldexp(len3, -3 * (l + 2));
-    double ss[2], mx[2], rr[2][2];
 #pragma unroll
-    for (int sl = 0; sl < 2; sl++) {
-        const int t = 2 * u + sl;
-        const int m = t & 3, j = (t >> 2) & 7, k = t >> 5;
-        ss[sl] = 0.0;
-        mx[sl] = 0.0;
-#pragma unroll
-        for (int c = 0; c < 2; c++) {
-            const int i = 2 * m + ((j + k + c) & 1);
-            const double rc = c ? (sl ? r1.y : r1.x) : (sl ? r0.y : r0.x);
-            double r = resid_of<double>(rc, sum_full<double>(P, H, i, j, k), P[c * 256 + t], inv_h2);
-            rr[c][sl] = r;
-            ss[sl] = fmadd(r, r, ss[sl]);
-            mx[sl] = nanmax(fabs(r), mx[sl]);
-        }
-    }
+    for (int e = 0; e < 4; e++) r[e] = resid_of<double>(f[e], r[e], own[e], inv_h2);
     if (OUT) {
-        reinterpret_cast<float2 *>(r_out + b * 512)[u] = make_float2((float)rr[0][0], (float)rr[0][1]);
-        reinterpret_cast<float2 *>(r_out + b * 512 + 256)[u] = make_float2((float)rr[1][0], (float)rr[1][1]);
+        reinterpret_cast<float2 *>(r_out + b * 512)[u] = make_float2((float)(odd ? r[1] : r[0]), (float)(odd ? r[3] : r[2]));
+        reinterpret_cast<float2 *>(r_out + b * 512 + 256)[u] = make_float2((float)(odd ? r[0] : r[1]), (float)(odd ? r[2] : r[3]));
     }
-#pragma unroll
-    for (int off = 16; off > 0; off >>= 1) {
-#pragma unroll
-        for (int sl = 0; sl < 2; sl++) {
-            ss[sl] += __shfl_xor(ss[sl], off);
-            mx[sl] = nanmax(__shfl_xor(mx[sl], off), mx[sl]);
-        }
-    }
-    const double st = ss[0] + ss[1], mt = nanmax(mx[1], mx[0]);
-    if ((u & 31) == 0) {
-        S[u >> 5] = st;
-        M[u >> 5] = mt;
-    }
+    full_norms(r, odd, S, M);
     __syncthreads();
     if (u == 0) {
         partial[2 * q] = ((S[0] + S[1]) + (S[2] + S[3])) * vol;
