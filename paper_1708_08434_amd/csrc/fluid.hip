@@ -234,13 +234,29 @@ __global__ __launch_bounds__(64) void k_fluid_cf(Geo g, const double *__restrict
     o[192 + q] = vel;
 }
 
+// fn with the axis a (wave-uniform) as a compile-time constant
+template <int A> struct Axis { static constexpr int a = A; };
+template <typename F> __device__ __forceinline__ void with_axis(int a, F fn) {
+    if (a == 0)
+        fn(Axis<0>());
+    else if (a == 1)
+        fn(Axis<1>());
+    else
+        fn(Axis<2>());
+}
+
 // One leaf box per workgroup, one cell per thread: the densities with two
 // ghost layers and |E| with one in LDS, every face flux and velocity of the
 // box, then the update of the cell, the solver's right-hand side
-// -e (n_i - n_e) / eps0 and the box's time-step bound.
+// -e (n_i - n_e) / eps0 and the box's time-step bound.  Bound by the issue of
+// vector instructions, so the work is dealt to whole waves with all that is
+// uniform in scalars: wave d < 6 stages the ghosts of face d, and the 27 layers
+// of faces (axis a, position f) go round the 8 waves, the field values of the
+// next loaded before the work on one.  7876 boxes: 137 us with every thread
+// finding its own faces and ghosts, now 124 (the bytes take 73).
 __global__ __launch_bounds__(512) void k_fluid_update(
-    Geo g, const int32_t *__restrict__ isleaf, const int32_t *__restrict__ cfrev,
-    const int32_t *__restrict__ leaf, int64_t nleaf, const double *__restrict__ ne,
+    Geo g, const int32_t *__restrict__ cfrev, const int32_t *__restrict__ leaf, int64_t nleaf,
+    const double *__restrict__ ne,
     const double *__restrict__ ni, const double *__restrict__ n0e, const double *__restrict__ n0i,
     const double *__restrict__ ef, const double *__restrict__ en, FluidTable T,
     const double *__restrict__ cf, double dt, double wa, double wb, double *__restrict__ oute,
@@ -252,84 +268,77 @@ __global__ __launch_bounds__(512) void k_fluid_update(
     int t = threadIdx.x, i = t & 7, j = (t >> 3) & 7, k = t >> 6;
     auto p2 = [](int x, int y, int z) { return ((z + 2) * 12 + (y + 2)) * 12 + (x + 2); };
     auto p1 = [](int x, int y, int z) { return ((z + 1) * 10 + (y + 1)) * 10 + (x + 1); };
-    int nb[6], sl[6];
-#pragma unroll
-    for (int d = 0; d < 6; d++) {
-        nb[d] = g.nbr[b * 6 + d];
-        sl[d] = g.cfslot[b * 6 + d];
-    }
+    const int32_t *nb = g.nbr + b * 6, *sl = g.cfslot + b * 6;
     double h = cell_h(g, g.ijk[b * 4 + 3]), inv_h = 1.0 / h;
     double nec = ne[b * 512 + t], nic = ni[b * 512 + t], n0ec = n0e[b * 512 + t], n0ic = n0i[b * 512 + t];
     double enc = en[b * 512 + t];
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6), qq = t & 63, u = qq & 7, v = qq >> 3;
+    double efv = ef[(b * 27 + w) * 64 + qq];
+    if (w < 6) {
+        // face w: two layers of densities, and one of |E|: the same-level cell,
+        // the mirrored cell, or the coarse cell holding the ghost
+        with_axis(w >> 1, [&](auto A) __attribute__((always_inline)) {
+            constexpr int a = decltype(A)::a;
+            const int side = w & 1, nbd = nb[w], sld = sl[w];
+            double v0, v1, ve;
+            if (nbd == -1) {
+                const int32_t *x = g.slotx + 8 * (int64_t)sld;
+                v0 = cf[(int64_t)sld * 256 + qq];
+                v1 = cf[(int64_t)sld * 256 + 64 + qq];
+                ve = en[(int64_t)x[0] * 512 + natc(place(a, side ? 0 : 7, x[1] + (u >> 1), x[2] + (v >> 1)))];
+            } else {
+                // a neighbour's layers from the common face, or the box's own
+                const int64_t q0 = (nbd >= 0 ? (int64_t)nbd : b) * 512;
+                const bool low = (nbd >= 0) == (side != 0);  // layers 0, 1 (else 7, 6)
+                v0 = ne[q0 + natc(place(a, low ? 0 : 7, u, v))];
+                v1 = ne[q0 + natc(place(a, low ? 1 : 6, u, v))];
+                ve = en[q0 + natc(place(a, low ? 0 : 7, u, v))];
+            }
+            const Cell c0 = place(a, side ? 8 : -1, u, v), c1 = place(a, side ? 9 : -2, u, v);
+            N[p2(c0.x, c0.y, c0.z)] = v0;
+            N[p2(c1.x, c1.y, c1.z)] = v1;
+            EN[p1(c0.x, c0.y, c0.z)] = ve;
+        });
+    }
     N[p2(i, j, k)] = nec;
     EN[p1(i, j, k)] = enc;
-    // density ghosts: face d, layer L (0 adjacent), face cell (u, v)
-    for (int e = t; e < 768; e += 512) {
-        int d = e >> 7, L = (e >> 6) & 1, qq = e & 63, a = d >> 1, side = d & 1;
-        int u = qq & 7, v = qq >> 3;
-        int nbd = d == 0 ? nb[0] : d == 1 ? nb[1] : d == 2 ? nb[2] : d == 3 ? nb[3] : d == 4 ? nb[4] : nb[5];
-        int sld = d == 0 ? sl[0] : d == 1 ? sl[1] : d == 2 ? sl[2] : d == 3 ? sl[3] : d == 4 ? sl[4] : sl[5];
-        double val;
-        if (nbd >= 0) {
-            val = ne[(int64_t)nbd * 512 + natc(place(a, side ? L : 7 - L, u, v))];
-        } else if (nbd == -2) {
-            val = ne[b * 512 + natc(place(a, side ? 7 - L : L, u, v))];
-        } else {
-            val = cf[(int64_t)sld * 256 + L * 64 + qq];
-        }
-        Cell c = place(a, side ? 8 + L : -1 - L, u, v);
-        N[p2(c.x, c.y, c.z)] = val;
-    }
-    // |E| ghosts (one layer): the same-level cell, the mirrored cell, or the
-    // coarse cell holding the ghost
-    if (t < 384) {
-        int d = t >> 6, qq = t & 63, a = d >> 1, side = d & 1;
-        int u = qq & 7, v = qq >> 3;
-        int nbd = d == 0 ? nb[0] : d == 1 ? nb[1] : d == 2 ? nb[2] : d == 3 ? nb[3] : d == 4 ? nb[4] : nb[5];
-        int sld = d == 0 ? sl[0] : d == 1 ? sl[1] : d == 2 ? sl[2] : d == 3 ? sl[3] : d == 4 ? sl[4] : sl[5];
-        double val;
-        if (nbd >= 0) {
-            val = en[(int64_t)nbd * 512 + natc(place(a, side ? 0 : 7, u, v))];
-        } else if (nbd == -2) {
-            val = en[b * 512 + natc(place(a, side ? 7 : 0, u, v))];
-        } else {
-            const int32_t *x = g.slotx + 8 * (int64_t)sld;
-            val = en[(int64_t)x[0] * 512 + natc(place(a, side ? 0 : 7, x[1] + (u >> 1), x[2] + (v >> 1)))];
-        }
-        Cell c = place(a, side ? 8 : -1, u, v);
-        EN[p1(c.x, c.y, c.z)] = val;
-    }
     __syncthreads();
     // faces: axis a, face f = 0..8 (between cells f-1 and f), cell (u, v)
-    for (int e = t; e < 1728; e += 512) {
-        int a = e / 576, r = e - 576 * a, f = r >> 6, qq = r & 63;
-        int u = qq & 7, v = qq >> 3;
-        Cell cl = place(a, f - 1, u, v), cr = place(a, f, u, v);
-        double eL = EN[p1(cl.x, cl.y, cl.z)], eR = EN[p1(cr.x, cr.y, cr.z)];
-        double mu, D;
-        coef2(T, 0.5 * (eL + eR), mu, D);
-        double V = -mu * ef[((b * 3 + a) * 9 + f) * 64 + qq], F;
-        int d = 2 * a + (f == 8 ? 1 : 0);
-        int nbd = d == 0 ? nb[0] : d == 1 ? nb[1] : d == 2 ? nb[2] : d == 3 ? nb[3] : d == 4 ? nb[4] : nb[5];
-        int sld = d == 0 ? sl[0] : d == 1 ? sl[1] : d == 2 ? sl[2] : d == 3 ? sl[3] : d == 4 ? sl[4] : sl[5];
-        bool bnd = f == 0 || f == 8;
-        if (bnd && nbd == -1) {  // fine side of a refinement boundary
-            F = cf[(int64_t)sld * 256 + 128 + qq];
-            V = cf[(int64_t)sld * 256 + 192 + qq];
-        } else if (bnd && nbd >= 0 && !isleaf[nbd]) {  // coarse side: mean of the 4 fine fluxes
-            int64_t fs = cfrev[(b * 6 + d) * 4 + (v >> 2) * 2 + (u >> 2)];
-            double s = 0.0;
-            for (int dv = 0; dv < 2; dv++)
-                for (int du = 0; du < 2; du++)
-                    s += cf[fs * 256 + 128 + ((2 * v + dv) & 7) * 8 + ((2 * u + du) & 7)];
-            F = 0.25 * s;
-        } else {
-            Cell c0 = place(a, f - 2, u, v), c3 = place(a, f + 1, u, v);
-            F = flux(N[p2(c0.x, c0.y, c0.z)], N[p2(cl.x, cl.y, cl.z)], N[p2(cr.x, cr.y, cr.z)],
-                     N[p2(c3.x, c3.y, c3.z)], V, D, inv_h);
-        }
-        FX[e] = F;
-        VX[e] = V;
+#pragma unroll 1
+    for (int id = w; id < 27; id += 8) {
+        const double ea = efv;
+        if (id + 8 < 27) efv = ef[(b * 27 + id + 8) * 64 + qq];
+        with_axis(id / 9, [&](auto A) __attribute__((always_inline)) {
+            constexpr int a = decltype(A)::a;
+            const int f = id - 9 * a;
+            constexpr int sn = a == 0 ? 1 : a == 1 ? 12 : 144, se = a == 0 ? 1 : a == 1 ? 10 : 100;
+            const Cell c0 = place(a, -2, u, v), c1 = place(a, -1, u, v);
+            const double *n = N + p2(c0.x, c0.y, c0.z) + f * sn, *e = EN + p1(c1.x, c1.y, c1.z) + f * se;
+            double mu, D;
+            coef2(T, 0.5 * (e[0] + e[se]), mu, D);
+            double V = -mu * ea, F;
+            const int d = 2 * a + (f == 8);
+            int nbd = 0, sld = 0;  // of a face of the box
+            if (f == 0 || f == 8) {
+                nbd = nb[d];
+                sld = sl[d];
+            }
+            if (nbd == -1) {  // fine side of a refinement boundary
+                F = cf[(int64_t)sld * 256 + 128 + qq];
+                V = cf[(int64_t)sld * 256 + 192 + qq];
+            } else if (sld == -2) {  // coarse side (the neighbour has children): mean of the 4 fine fluxes
+                int64_t fs = cfrev[(b * 6 + d) * 4 + (v >> 2) * 2 + (u >> 2)];
+                double s = 0.0;
+                for (int dv = 0; dv < 2; dv++)
+                    for (int du = 0; du < 2; du++)
+                        s += cf[fs * 256 + 128 + ((2 * v + dv) & 7) * 8 + ((2 * u + du) & 7)];
+                F = 0.25 * s;
+            } else {
+                F = flux(n[0], n[sn], n[2 * sn], n[3 * sn], V, D, inv_h);
+            }
+            FX[id * 64 + qq] = F;
+            VX[id * 64 + qq] = V;
+        });
     }
     __syncthreads();
     double div = 0.0, vs = 0.0;
@@ -400,7 +409,7 @@ void launch_fluid_stage(const Geo &g, const FluidArgs &A, hipStream_t s) {
                            A.en, A.tab, A.slots, A.nslot, A.cf);
     if (A.nleaf > 0) {
         hipLaunchKernelGGL(k_fluid_update, dim3((unsigned)(8 * ((A.nleaf + 7) >> 3))), dim3(512), 0, s, g,
-                           A.isleaf, A.cfrev, A.leaf, A.nleaf, (const double *)A.ne, A.ni, A.n0e, A.n0i,
+                           A.cfrev, A.leaf, A.nleaf, (const double *)A.ne, A.ni, A.n0e, A.n0i,
                            A.ef, A.en, A.tab, (const double *)A.cf, A.dt, A.wa, A.wb, A.oute, A.outi,
                            A.rhs, A.partial);
         hipLaunchKernelGGL(k_fluid_min, dim3(1), dim3(1024), 0, s, (const double *)A.partial, A.nleaf,

@@ -181,7 +181,7 @@ struct FluidTable {
 };
 struct FluidArgs {
     FluidTable tab;
-    const int32_t *isleaf, *cfrev, *leaf, *slots;  // cfrev: [n][6][4] fine slots of a coarse face
+    const int32_t *cfrev, *leaf, *slots;  // cfrev: [n][6][4] fine slots of a coarse face
     int64_t nleaf, nslot;
     double *ne;                                    // covered cells overwritten (mean of children)
     const double *ni, *n0e, *n0i, *ef, *en;

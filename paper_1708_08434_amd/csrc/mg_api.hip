@@ -1716,7 +1716,6 @@ int fluid_stage(mg_tree *t, const double *ef, const double *en, double *ne, cons
     hipStream_t s = stream_of(t);
     FluidArgs A;
     A.tab = {fdp(t, t->foff.tab), t->ntab, (double)(t->ntab - 1) / t->emax};
-    A.isleaf = t->d.isleaf;
     A.cfrev = fip(t, t->foff.cfrev);
     A.leaf = t->d.leaf;
     A.slots = t->d.slots;
