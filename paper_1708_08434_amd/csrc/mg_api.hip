@@ -830,7 +830,7 @@ int learned_step_impl(mg_tree *t, mg_nn *nn, const LearnedWs &L, double *steps_h
         restrict_all(t, F);
         norms_launch(t, 0, E.rhs);
     }
-    launch_nn_gather(E.rhs, t->d.leaf, nl, t->d.nbr, t->d.ijk, t->d.isleaf, t->dom.len, L.x, L.scale, s);
+    launch_nn_gather(E.rhs, t->d.leaf, nl, t->d.nbr, t->d.cfslot, t->d.ijk, t->dom.len, L.x, L.scale, s);
     launch_nn_forward(nn->prm, nn->pk, nl, nullptr, L.x, L.y, nullptr, nullptr, s);
     // the correction on the leaf boxes, its means on the covered cells that a
     // leaf box or a c_hat reads (those of a stopping test)
@@ -928,7 +928,7 @@ int learned_level_step(mg_tree *t, mg_nn *nn, const LearnedWs &L, int l, double 
     const int32_t *list = t->d.leaf + q0;
     ensure_cf(t, F, l);
     launch_leaf_norms(F.g, F.phi, F.rhs, F.chat, list, nq, L.partial, E.rhs, s);  // r in FP32
-    launch_nn_gather(E.rhs, list, nq, t->d.nbr, t->d.ijk, t->d.isleaf, t->dom.len, L.x, L.scale, s);
+    launch_nn_gather(E.rhs, list, nq, t->d.nbr, t->d.cfslot, t->d.ijk, t->dom.len, L.x, L.scale, s);
     launch_nn_forward(nn->prm, nn->pk, nq, nullptr, L.x, L.y, nullptr, nullptr, s);
     launch_nn_scatter(L.y, L.scale, list, nq, E.phi, s);
     int64_t c0 = t->sstart[l], nc = t->sstart[l + 1] - c0;
@@ -2371,7 +2371,7 @@ int mg_nn_inputs(mg_tree *t, float *x, float *scale) {
     Fields<float> E = f32(t);
     restrict_all(t, f64(t));
     norms_launch(t, 0, E.rhs);
-    launch_nn_gather(E.rhs, t->d.leaf, t->nleaf, t->d.nbr, t->d.ijk, t->d.isleaf, t->dom.len, x, scale,
+    launch_nn_gather(E.rhs, t->d.leaf, t->nleaf, t->d.nbr, t->d.cfslot, t->d.ijk, t->dom.len, x, scale,
                      stream_of(t));
     return hip_check(hipGetLastError(), "input gather");
 }

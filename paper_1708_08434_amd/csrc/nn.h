@@ -46,8 +46,7 @@ void launch_nn_adam(float *prm, float *m, float *v, const float *g, float lr, fl
 
 // Learned step on a tree (leaf boxes in leaf-list order, fields colour-split).
 void launch_nn_gather(const float *r32, const int32_t *leaf, int64_t nleaf, const int32_t *nbr,
-                      const int32_t *ijk4, const int32_t *isleaf, double len, float *x, float *scale,
-                      hipStream_t s);
+                      const int32_t *cfslot, const int32_t *ijk4, double len, float *x, float *scale, hipStream_t s);
 void launch_nn_scatter(const float *y, const float *scale, const int32_t *leaf, int64_t nleaf, float *e32,
                        hipStream_t s);
 void launch_nn_dots1(const float *r32, const float *q, const int32_t *list, int64_t n, const int32_t *ijk4,
