@@ -93,7 +93,8 @@ typedef struct {
 int mg_tree_create(mg_tree **out, const mg_domain *dom, int64_t n, const int32_t *level,
                    const int32_t *ijk, const int32_t *tree);
 /* mg_tree_destroy synchronises the bound stream (work enqueued without a
- * host wait may still be running), then frees the host state. */
+ * host wait may still be running), the null stream too, then frees the host
+ * state. */
 int mg_tree_destroy(mg_tree *t);
 int mg_tree_info(const mg_tree *t, mg_tree_info_t *info);
 
@@ -105,9 +106,10 @@ int mg_tree_info(const mg_tree *t, mg_tree_info_t *info);
  * host staging buffer, zeroes the fields, and waits for both on the stream
  * before returning.  The staging buffer (the tables' size, a few hundred
  * bytes per box) is pooled: the library keeps the largest one it has used
- * until the process ends.  The workspace must stay valid until rebind or
- * destroy.  On an error the tree is left unbound (MG_ESTATE from the calls
- * that need a workspace until a bind succeeds).
+ * until the process ends.  A tree that is bound already first waits for its
+ * old stream.  The workspace must stay valid until rebind or destroy.  On an
+ * error the tree is left unbound (MG_ESTATE from the calls that need a
+ * workspace until a bind succeeds).
  */
 int mg_tree_bind(mg_tree *t, void *ws, int64_t ws_bytes, void *stream);
 

@@ -1131,8 +1131,8 @@ int mg_tree_create(mg_tree **out, const mg_domain *dom, int64_t n, const int32_t
 // Capture streams and pinned result buffers outlive the trees that used
 // them: a mesh adaptation creates and destroys a tree per step, and creating
 // a stream or a pinned buffer costs more than the new tree's table upload.
-// A destroyed tree hands them back (its bound stream has been synchronised,
-// and a capture stream never executes work); the next bind takes them.
+// A destroyed tree hands them back (after wait_bound: kernels write the result
+// buffer; a capture stream never executes work); the next bind takes them.
 std::mutex g_spare_mu;
 std::vector<std::pair<int, void *>> g_spare_streams;    // (device, stream)
 std::vector<std::pair<size_t, double *>> g_spare_pinned;  // (capacity, buffer)
@@ -1199,16 +1199,31 @@ void give_stage(char *p, size_t cap) {
     if (drop) (void)hipHostFree(drop);
 }
 
+// Waits for the work on the bound stream.  Calls without a host wait
+// (mg_vcycle without statistics, mg_fluid_stage without a limit, mg_nn_inputs,
+// mg_field_set) may have left some there that uses the graphs and writes the
+// pinned result buffer, so both stay until it has ended: before a destroy and
+// before a rebind.  Whether there is a stream is told by the workspace (the
+// null stream's handle is 0, and is one per device).  False if the wait failed.
+static bool wait_bound(const mg_tree *t) {
+    if (!t->ws) return true;
+    int dev = t->cap_device;
+    const bool other = hipGetDevice(&dev) == hipSuccess && dev != t->cap_device;
+    if (other) (void)hipSetDevice(t->cap_device);
+    const hipError_t e = hipStreamSynchronize((hipStream_t)t->stream);
+    if (other) (void)hipSetDevice(dev);
+    if (e != hipSuccess) (void)hipGetLastError();  // not the next launch's error
+    return e == hipSuccess;
+}
+
 int mg_tree_destroy(mg_tree *t) {
     if (!t) return MG_OK;
-    // work enqueued without a host wait (mg_vcycle without statistics,
-    // mg_fluid_step, mg_field_set) may still run on the bound stream and use
-    // the graphs and the pinned buffer released below
-    if (t->stream) (void)hipStreamSynchronize((hipStream_t)t->stream);
+    const bool idle = wait_bound(t);
     for (auto &g : t->graphs) drop_graph(g);
     {
         std::lock_guard<std::mutex> lk(g_spare_mu);
-        if (t->host_result) g_spare_pinned.push_back({t->host_result_bytes, t->host_result});
+        // (a buffer that may still be written is left allocated)
+        if (t->host_result && idle) g_spare_pinned.push_back({t->host_result_bytes, t->host_result});
         if (t->cap_stream) g_spare_streams.push_back({t->cap_device, t->cap_stream});
     }
     for (auto &p : t->probes) {
@@ -1275,6 +1290,7 @@ int mg_tree_bind(mg_tree *t, void *ws, int64_t bytes, void *stream) {
 }
 
 static int bind_tables(mg_tree *t, void *ws, void *stream) {
+    if (!wait_bound(t)) t->host_result = nullptr;  // may still be written: another is taken below
     for (auto &g : t->graphs) drop_graph(g);
     t->ws = ws;
     t->stream = stream;
