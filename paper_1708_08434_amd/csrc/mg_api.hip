@@ -1168,7 +1168,9 @@ int take_pinned(size_t bytes, double **out, size_t *cap) {
             }
     }
     *cap = std::max<size_t>(bytes, 4096);
-    return hip_check(hipHostMalloc((void **)out, *cap), "pinned host buffer");
+    // kernels write it, those of another device too (the pool serves all)
+    const unsigned flags = hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent;
+    return hip_check(hipHostMalloc((void **)out, *cap, flags), "pinned host buffer");
 }
 
 int take_stage(size_t bytes, char **out, size_t *cap) {

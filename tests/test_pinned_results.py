@@ -178,3 +178,21 @@ ws = bind(h, 0)
     assert used[0] not in used[1:]      # the rebind's failed wait
     assert used[2] not in used[3:]      # the destroy's failed wait
     assert used[3] == used[4]           # waited for: handed on
+
+
+def test_result_buffers_are_mapped_on_every_device(stand_in):
+    """Kernels of any device write to a pooled buffer, whichever device was
+    current when it was allocated: hipHostMallocPortable (1) and
+    hipHostMallocMapped (2)."""
+    log = calls(stand_in, """
+h = tree()
+ws = bind(h, 0)
+M.mg_tree_destroy(h)
+hip.hipSetDevice(1)
+h = tree()
+ws = bind(h, 0)
+""")
+    used = [s.split()[1] for s in log if s.startswith("result")]
+    assert len(used) == 2 and used[0] == used[1]
+    flags = [int(s.split()[3], 16) for s in log if s.startswith("pinned " + used[0])]
+    assert len(flags) == 1 and flags[0] & 3 == 3
