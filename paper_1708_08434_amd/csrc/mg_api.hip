@@ -124,11 +124,17 @@ void give_event(mg_tree *t, hipEvent_t e) {
 // fused sweep is one launch instead of two and also forms the level's FAS
 // right-hand side; large ones by HBM, where half-sweeps reach the copy rate,
 // need no prolongation pass, and in FP32 gain from octets (half the ghost
-// loads).  Whole FP64 solves with fused sweeps up to that level, against the
-// same with that level in half-sweeps: 1024 boxes and below 3246 : 3910 us, 1792
-// boxes 3151 : 3246, 4960 boxes 3096 : 3141; but 5216 boxes 5843 : 5732 and 5888
-// boxes 36663 : 36608, so the line lies at 5000.  FP32 above it: octets 9220,
-// one-box half-sweeps 9450 us.
+// loads).  The line comes from trees of three nested levels of about N boxes
+// (balls, long and flat ellipsoids and forests of three on a uniform tree),
+// whole solves with these three levels in half-sweeps (FP32: octets), against
+// fused sweeps, in per cent of the time:
+//   N       800 1400 2000 2650 3500 3800 4500 4700 5600 6900 7300 9600 12500 17000 24500
+//   FP64    +18  +12   +6   +5   +3   +2   +3 +1.5   -2 -0.5   -3   -2    -3    -3   -10
+//   FP32    +24  +16   +9   +7   +6   +5   +4   +3 -0.6   -1   -5   -3    -5    -7   -10
+// (a solve at N = 3500: FP64 3316 us fused, 3414 in half-sweeps, FP32 2923 and
+// 3103; at 7300: 4791 and 4632, 4100 and 3908).  Both change sign near 5000,
+// which is the line of both.  One-box half-sweeps instead of octets in FP32: up
+// to 2% faster below 4000 boxes, 1% slower at 7300, 6% at 100000.
 constexpr int64_t kFusedMaxBoxes = 5000;
 void default_schedule(mg_tree *t) {
     for (int l = 2; l <= t->nlev; l++) {

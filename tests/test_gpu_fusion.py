@@ -121,6 +121,63 @@ def test_default_schedule_gives_the_half_sweeps_bits():
 
 
 @pytest.mark.parametrize("prec", [M.MG_FP64, M.MG_MIXED])
+def test_default_schedule_on_both_sides_of_its_line(prec):
+    """A tree whose default schedule has fused sweeps on its lower levels and
+    half-sweeps (FP32: octets) on the finest, so that a cycle passes from one
+    to the other: the bits of half-sweeps on every level, and other launches
+    than either kind on all levels."""
+    c = np.array([7.6, 8.1, 8.3])
+    ball = [(5, i, j, k) for i in range(16) for j in range(16) for k in range(16)
+            if np.linalg.norm(np.array([i, j, k]) + 0.5 - c) < 5.9]
+    bl = refine_boxes_explicit(5, ball)
+    g = M.Tree(bl.level, bl.ijk, bl.tree, bc_type=(0, 0, 1, 0, 0, 0), bc_val=(0, 0, 0, 0, 0, 1.0))
+    count = np.bincount(g.index(M.MG_IDX_LEVEL))
+    assert g.nlev == 6 and count[5] <= 4096 and count[6] >= 6000
+    g.set_field(M.MG_FIELD_RHS, np.random.default_rng(8).standard_normal((g.n, 8, 8, 8)) * 100.0)
+    say("default schedule", list(count[1:]), prec)
+    got = []
+    for sch in (None, [3] * g.nlev, [3] + [7] * (g.nlev - 1), [3] + [9] * (g.nlev - 1)):
+        if sch:
+            M.mg_set_schedule(g.h, prec, sch)
+        st = g.fmg_solve(precision=prec)
+        got.append((st["n_vcycles"], g.get_field(M.MG_FIELD_PHI), (st["launches_fmg"], st["launches_cycle"])))
+    for k, p, n in got[1:]:
+        assert k == got[0][0] and np.array_equal(p, got[0][1])
+        assert n != got[0][2]
+
+
+@pytest.mark.parametrize("sweeps", [(2, 2), (1, 3), (3, 1), (4, 2)])
+@pytest.mark.parametrize("name", ["uniform64", "streamer_small", "bcval", "forest3", "neumann_sides"])
+def test_fused_schedules_give_the_half_sweeps_bits(name, sweeps):
+    """Both fused variants on every level (the schedule that small trees start
+    with) against half-sweeps that are set by name, for even and odd numbers
+    of sweeps: single cycles, smoothing and whole solves."""
+    g, rhs = make_tree(name)
+    phi0 = np.random.default_rng(12).standard_normal((g.n, 8, 8, 8))
+    say("fused against half-sweeps", name, sweeps, g.n, "boxes")
+    got = []
+    for v in (3,) + M.MG_GSRB_FUSED:
+        out = []
+        for prec in (M.MG_FP64, M.MG_MIXED):
+            M.mg_set_schedule(g.h, prec, [3] + [v] * (g.nlev - 1))
+        for f_phi, f_rhs, opf in ((M.MG_FIELD_PHI, M.MG_FIELD_RHS, 0), (M.MG_FIELD_E32, M.MG_FIELD_R32, M.MG_OP_F32)):
+            g.set_field(f_phi, phi0)
+            g.set_field(f_rhs, rhs)
+            g.step(M.MG_OP_SMOOTH | opf, g.nlev, sweeps[1])
+            g.step(M.MG_OP_VCYCLE | opf, g.nlev, sweeps[0])
+            out.append(g.get_field(f_phi))
+        g.set_field(M.MG_FIELD_RHS, rhs)
+        for prec in (M.MG_FP64, M.MG_MIXED):
+            st = g.fmg_solve(precision=prec, n_down=sweeps[0], n_up=sweeps[1])
+            out.append(g.get_field(M.MG_FIELD_PHI))
+            out.append(np.array([st["n_vcycles"]] + list(st["hist"])))
+        got.append(out)
+    for other in got[1:]:
+        for q, (a, b) in enumerate(zip(other, got[0])):
+            assert np.array_equal(a, b), (name, sweeps, q, np.abs(a - b).max())
+
+
+@pytest.mark.parametrize("prec", [M.MG_FP64, M.MG_MIXED])
 def test_schedules_agree_where_h_is_no_power_of_two(prec):
     """Step by step in half-sweeps against the one-launch bottom with fused
     sweeps, half-sweeps and octets, on a domain of length 0.04: there h^2 b
