@@ -467,7 +467,7 @@ int mg_timing_read(mg_tree *t, mg_kernel_timing_t *out);
  * (MG_MIXED) kernels.  The field being swept is parked and restored, so the
  * solver state is unchanged.  schedule (host, [n_levels], may be NULL)
  * receives the chosen variant per level (index level-1); mg_set_schedule
- * applies a stored schedule (e.g. from a cache keyed by the tree's level
+ * applies a stored schedule (e.g. from a cache keyed by the build and the level
  * sizes) and rejects entries outside 0..MG_GSRB_VARIANTS-1.  A tree starts
  * with variants chosen by the number of boxes of each level.  All variants
  * compute the same values.

@@ -2,11 +2,14 @@
 
 The search itself runs in the library (mg_autotune: every launch variant of
 the half-sweep kernel timed per level with HIP events).  This module keys the
-result by the device name, the precision and the tree's boxes per level, and
-stores it in a JSON file ($MG_TUNE_CACHE, default
+result by the device name, the library build, the precision and the tree's
+boxes per level, and stores it in a JSON file ($MG_TUNE_CACHE, default
 ~/.cache/paper_1708_08434_amd/tune.json) so later runs on the same tree shape
-skip the search.
+skip the search.  The build is part of the key because a schedule is only the
+fastest one for the kernels it was timed on.
 """
+import functools
+import hashlib
 import json
 import os
 
@@ -19,12 +22,18 @@ def cache_path():
                                        "tune.json"))
 
 
+@functools.lru_cache(maxsize=8)
+def _build_id(path):
+    with open(path, "rb") as f:
+        return hashlib.sha256(f.read()).hexdigest()[:16]
+
+
 def _key(tree, precision):
     import torch
     dev = torch.cuda.get_device_name(tree.device)
     ls = list(tree.info.level_start[:tree.nlev + 1])
     counts = [int(ls[i + 1] - ls[i]) for i in range(tree.nlev)]
-    return f"{dev}|{M.MG_GSRB_VARIANTS} variants|{'mixed' if precision == M.MG_MIXED else 'fp64'}|{counts}"
+    return f"{dev}|{M.MG_GSRB_VARIANTS} variants|build {_build_id(M.LIB_PATH)}|{'mixed' if precision == M.MG_MIXED else 'fp64'}|{counts}"
 
 
 def tune(tree, precision=M.MG_FP64, reps=16, use_cache=True):

@@ -215,6 +215,34 @@ def test_schedule_entries_are_validated():
         M.mg_tree_destroy(h)
 
 
+def test_cached_schedules_belong_to_the_kernels_they_were_timed_on(tmp_path, monkeypatch):
+    """autotune.tune takes a cached schedule for the same tree shape, device
+    and library only: a rebuilt library with other kernels searches again,
+    and keeps the other library's entry."""
+    import json
+    import types
+    import torch
+    from paper_1708_08434_amd import autotune
+    searched, applied = [], []
+    monkeypatch.setattr(torch.cuda, "get_device_name", lambda d: "some GPU")
+    monkeypatch.setattr(M, "mg_autotune", lambda h, prec, reps, nlev: searched.append(1) or [3] * nlev)
+    monkeypatch.setattr(M, "mg_set_schedule", lambda h, prec, s: applied.append(s))
+    monkeypatch.setenv("MG_TUNE_CACHE", str(tmp_path / "tune.json"))
+    tree = types.SimpleNamespace(device="cuda", nlev=2, h=None, info=types.SimpleNamespace(level_start=[0, 1, 9]))
+    # an entry from before the library took part in the key
+    old = f"some GPU|{M.MG_GSRB_VARIANTS} variants|fp64|[1, 8]"
+    (tmp_path / "tune.json").write_text(json.dumps({old: [5, 5]}))
+    for n, content in ((1, b"one"), (2, b"two")):
+        lib = tmp_path / f"lib{n}.so"
+        lib.write_bytes(content)
+        monkeypatch.setattr(M, "LIB_PATH", str(lib))
+        assert autotune.tune(tree) == ([3, 3], False) and len(searched) == n
+        assert autotune.tune(tree) == ([3, 3], True) and len(searched) == n
+    monkeypatch.setattr(M, "LIB_PATH", str(tmp_path / "lib1.so"))
+    assert autotune.tune(tree) == ([3, 3], True)
+    assert applied == [[3, 3]] * 3
+
+
 def test_workload_leaf_counts_match_the_tables():
     """The generators' leaf count (used for neutrality and for cells/s) equals
     the leaf count of the library's and the oracle's own tables on a deep
