@@ -19,6 +19,7 @@
 // four fine fluxes on each of its face cells, so no mass is lost there.
 #include <hip/hip_runtime.h>
 
+#include "axis.h"
 #include "kernels.h"
 
 namespace mg {
@@ -232,17 +233,6 @@ __global__ __launch_bounds__(64) void k_fluid_cf(Geo g, const double *__restrict
     o[64 + q] = gh[1];
     o[128 + q] = flux(m2, m1, p0, p1, vel, D, inv_h);
     o[192 + q] = vel;
-}
-
-// fn with the axis a (wave-uniform) as a compile-time constant
-template <int A> struct Axis { static constexpr int a = A; };
-template <typename F> __device__ __forceinline__ void with_axis(int a, F fn) {
-    if (a == 0)
-        fn(Axis<0>());
-    else if (a == 1)
-        fn(Axis<1>());
-    else
-        fn(Axis<2>());
 }
 
 // One leaf box per workgroup, one cell per thread: the densities with two

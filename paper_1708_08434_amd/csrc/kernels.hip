@@ -18,6 +18,7 @@
 // of each other, so a kernel costs one memory round trip plus one barrier.
 #include <cmath>
 
+#include "axis.h"
 #include "kernels.h"
 
 namespace mg {
@@ -571,16 +572,6 @@ template <int A> __device__ __forceinline__ int face_place(int layer, int u, int
            : A == 1 ? (v + 2) * 72 + (layer + 2) * 6 + ((u + 2) >> 1)
                     : (layer + 2) * 72 + (v + 2) * 6 + ((u + 2) >> 1);
 }
-// fn with the axis w (wave-uniform) as a compile-time constant
-template <int A> struct Axis { static constexpr int a = A; };
-template <typename F> __device__ __forceinline__ void with_axis(int w, F fn) {
-    if (w == 0)
-        fn(Axis<0>());
-    else if (w == 1)
-        fn(Axis<1>());
-    else
-        fn(Axis<2>());
-}
 
 template <typename T, bool FAS>
 __global__ __launch_bounds__(256) void k_gsrb_sweep(Geo g, const T *__restrict__ src,
@@ -1027,14 +1018,6 @@ __device__ __forceinline__ void full_norms(const double r[4], bool odd, double *
 // the box also writes its volume-weighted sum of r^2 and max |r| at its leaf
 // position leafpos[b] of `partial`, with the arithmetic and the summation
 // order of k_leaf_norms (the norm the stopping test divides by).
-template <typename T>
-__device__ __forceinline__ T ghost_of_zero(const Geo &g, const T *__restrict__ chat, int64_t b, int d, int nb,
-                                           int slot, int u, int v) {
-    if (nb >= 0) return (T)0;
-    if (nb == -2) return g.bct[d] == 1 ? (T)0 : dirichlet_ghost<T>(bc_value<T>(g, b, d, u, v), (T)0);
-    return cf_ghost<T>(chat[(int64_t)slot * 64 + v * 8 + u], (T)0, (T)0);
-}
-
 template <typename T, bool ZERO>
 __global__ __launch_bounds__(128) void k_resid_restrict(Geo g, T *__restrict__ phi, T *__restrict__ rhs,
                                                         T *__restrict__ old, const T *__restrict__ chat,
