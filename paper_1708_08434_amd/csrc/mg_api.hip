@@ -744,7 +744,10 @@ int64_t learned_layout(const mg_tree *t, char *base, LearnedWs *L) {
     };
     int64_t nl = t->nleaf;
     int64_t ox = take(4 * 1000 * nl), oy = take(4 * 512 * nl), os = take(4 * nl);
-    int64_t oq = take(4 * 3 * 512 * nl), op = take(8 * 9 * nl);
+    // q: the operator image of the per-level step (one of the three the size
+    // has room for), or the chunk sums of the step on all levels (at most nine
+    // doubles a box); partial: the two sums a box of the per-level step
+    int64_t oq = take(4 * 3 * 512 * nl), op = take(8 * 2 * nl);
     int64_t ost = take(8 * (int64_t)t->ntree * kStepStride);
     if (base && L) {
         L->x = (float *)(base + ox);

@@ -58,6 +58,21 @@ def test_learned_host_side_sizes_and_errors():
     assert L.mg_nn_create(ctypes.byref(out), ctypes.c_void_p(256), 16, None) == M.MG_ENOMEM
 
 
+def test_learned_workspace_a_leaf_box():
+    """Bytes a leaf box of the learned workspace: input, output, scale, the
+    operator images and two sums (leaf counts that are multiples of 64, so
+    that the 256-byte rounding of each part adds nothing)."""
+    need = {}
+    for level in (3, 4):
+        bl = uniform_boxes(level)
+        h = M.mg_tree_create(M.make_domain(), bl.level, bl.ijk)
+        try:
+            need[8 ** (level - 1)] = NN.mg_learned_bytes(h)
+        finally:
+            M.mg_tree_destroy(h)
+    assert need[512] - need[64] == 448 * (4 * (1000 + 512 + 1 + 3 * 512) + 8 * 2)
+
+
 def forest():
     a = amr_tree()
     b = refine_boxes_explicit(2, [(2, 1, 1, 1)], tree=1)
