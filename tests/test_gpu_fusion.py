@@ -247,3 +247,25 @@ def test_solve_statistics_count_the_recorded_launches():
         assert 0 < c1 <= c0 and 0 < f1 <= f0
         assert f0 > c0 and f1 > c1
 
+
+def test_fusion_saves_launches_of_half_sweeps():
+    """The same count with half-sweeps on every level (a small tree starts
+    with fused sweeps, which have no fused prolongation or restriction): in
+    FP64 a cycle loses its restriction launch and the FMG pass its norm
+    pass, and no sequence launches more kernels."""
+    g, rhs = make_tree("streamer_small")
+    g.set_field(M.MG_FIELD_RHS, rhs)
+    got = {}
+    for prec in (M.MG_FP64, M.MG_MIXED):
+        M.mg_set_schedule(g.h, prec, [3] * g.nlev)
+        for flags in (0, M.MG_FUSE_ALL):
+            M.mg_set_fusion(g.h, flags)
+            st = g.fmg_solve(precision=prec)
+            got[flags, prec] = (st["launches_fmg"], st["launches_cycle"])
+            say("launches", flags, prec, got[flags, prec])
+    f0, c0 = got[0, M.MG_FP64]
+    f1, c1 = got[M.MG_FUSE_ALL, M.MG_FP64]
+    assert f1 < f0 and c1 < c0
+    f0, c0 = got[0, M.MG_MIXED]
+    f1, c1 = got[M.MG_FUSE_ALL, M.MG_MIXED]
+    assert f1 <= f0 and c1 <= c0
